@@ -75,14 +75,14 @@ extern "C" {
                                         cell width with the cell's own D, adding
                                         dt D / h^2 to the diagonal and that times E_B
                                         to the right-hand side.  Plans with Dirichlet
-                                        faces run one kernel per colour sweep (no
-                                        fused level kernels)                        */
+                                        faces run no marching kernels: small tiles, and
+                                        one kernel per colour sweep on large levels  */
 #define FLD_BC_PERIODIC         3    /* both faces of an axis: the ghosts are the cells at
                                         the other end and the face between the last
                                         and the first cell is an interior face (harmonic
                                         mean of their D).  One face of an axis periodic
                                         and the other not is INVALID_ARG.  Such plans
-                                        also sweep per colour                       */
+                                        sweep as those with Dirichlet faces         */
 #define FLD_BC_FIXED_GRADIENT   1    /* Neumann with the gradient dE/dx_a given in
                                         bc_grad (Sec. 3.4): ghosts continue the mirror
                                         image with that slope, E_{-k} = E_{k-1} -
@@ -157,11 +157,12 @@ typedef struct fld_opts {
                              INVALID_ARG if the tile does not fit the 160 KB LDS   */
     int32_t max_blocks;   /* cap on workgroups per persistent launch; 0 = 2048 [0]   */
     int32_t tile_depth;   /* fused 3D sweeps: planes per block, 16, 32 or 64; 0 = 32 [0] */
-    int32_t fused3_levels;/* 3D: the first k multigrid levels run fused sweeps, the
-                             coarser ones per-colour kernels; 0 = the levels whose
-                             sweep has at least 256 blocks [0].  3D grids use fused
-                             sweeps when fused = 1, nu1, nu2 >= 1 and nu1 + nu2 is
-                             even.  tile_rows, tile_wide, max_blocks, tile_depth and
+    int32_t fused3_levels;/* 3D: the first k multigrid levels run fused sweeps that march
+                             through the planes, the coarser ones several sweeps of a
+                             small tile per launch (per-colour kernels where that takes
+                             many tiles); 0 = the levels with more such tiles than compute
+                             units [0].  3D grids use both when fused is not 0, nu1, nu2
+                             >= 1 and nu1 + nu2 is even.  tile_rows, tile_wide, max_blocks, tile_depth and
                              fused3_levels must be 0 with autotune                  */
     double  bc_grad[6];   /* per face: the prescribed gradient of FLD_BC_FIXED_GRADIENT
                              faces (ignored on zero-flux faces) [0]                  */

@@ -161,7 +161,7 @@ int plan_autotune(Plan& p) {
     // the timed kernels read the plan's fields: give them finite values, and let
     // every grid take part
     FLD_HIP(hipDeviceSynchronize());
-    FLD_HIP(hipMemsetAsync(p.ws + p.table_bytes, 0, p.ws_bytes - p.table_bytes, nullptr));
+    FLD_HIP(hipMemsetAsync(p.ws + p.table_bytes, 0, p.bound_bytes() - p.table_bytes, nullptr));
     launch_set_active(p.dS, p.ngrids(), 1, nullptr);
     hipEvent_t e0, e1;
     FLD_HIP(hipEventCreate(&e0));

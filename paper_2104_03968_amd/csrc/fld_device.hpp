@@ -91,6 +91,37 @@ __host__ __device__ inline int32_t sweep3_tiles(const int32_t n[3], bool restr, 
     return ((n[0] + fx - 1) / fx) * ((n[1] + fy - 1) / fy) * ((n[2] + fz - 1) / fz);
 }
 
+// Two-sweep z-march (k_march3): a window of m3_px x m3_py positions, with a halo of four, and
+// its ring of kM3R LDS planes.  One position a thread, the two colour classes in wavefronts of
+// their own (m3_class threads each): 1024 threads in FP32; in FP64 the planes in flight take
+// more registers than 128, which leaves 768 threads and a smaller window.
+constexpr int kM3H = 4, kM3R = 6;
+__host__ __device__ constexpr int m3_px(int word) { return 40; }
+__host__ __device__ constexpr int m3_py(int word) { return 24; }
+__host__ __device__ constexpr int m3_class(int word) { return 512; }
+static_assert(m3_px(4) / 2 * (m3_py(4) + 1) <= m3_class(4) && (m3_px(4) / 2 + 1) * m3_py(4) <= m3_class(4) &&
+                  m3_px(8) / 2 * (m3_py(8) + 1) <= m3_class(8) && (m3_px(8) / 2 + 1) * m3_py(8) <= m3_class(8),
+              "a class' positions, and a row or a pair of columns of faces more");
+__host__ __device__ inline int32_t march3_tiles(const int32_t n[3], int word, int fz) {
+    const int fx = m3_px(word) - 2 * kM3H, fy = m3_py(word) - 2 * kM3H;
+    return ((n[0] + fx - 1) / fx) * ((n[1] + fy - 1) / fy) * ((n[2] + fz - 1) / fz);
+}
+
+// Small-level passes (k_tile): a workgroup's window of kTileCells positions, tile_p(dim) a
+// side, whose outer tile_halo(ns) rings are recomputed: ns sweeps from zero with the
+// restriction, or from an iterate without it, spoil 2 ns of them (a single sweep also
+// restricts from an iterate).  The interior's side is even, so tiles hold whole coarse cells.
+constexpr int kTileThreads = 1024;
+constexpr int kTileCells = 4096;
+constexpr int kTileMaxNs = 3;
+__host__ __device__ constexpr int tile_p(int dim) { return dim == 3 ? 16 : 64; }
+__host__ __device__ constexpr int tile_halo(int ns) { return ns == 1 ? 3 : 2 * ns; }
+__host__ __device__ constexpr int tile_hx(int ns) { return ns == 1 ? 4 : 2 * ns; }     // even: pairs of columns
+__host__ __device__ inline int32_t tile_tiles(const int32_t n[3], int dim, int ns) {
+    const int fx = tile_p(dim) - 2 * tile_hx(ns), f = tile_p(dim) - 2 * tile_halo(ns);
+    return ((n[0] + fx - 1) / fx) * ((n[1] + f - 1) / f) * (dim == 3 ? (n[2] + f - 1) / f : 1);
+}
+
 // z-march CG direction update (3D level 0): a window of kPqPX x kPqPY positions, 64 x 13
 // interior columns with one halo position around them, fz planes per block.
 constexpr int kPqPX = 66;
@@ -339,6 +370,18 @@ bool fused3_supported(bool fp32);
 // residual): each window also leaves its partial of b . x (r . z) in the level's partials
 void launch_sweep3(bool fp32, const LevelDesc* L, const GridState* S, JobList jl, int mode, int c0,
                    int from_xs, int fz, int nblk, hipStream_t s, int rz = 0);
+// Two red-black sweeps of a 3D level per launch, as a z-march of fz (even) planes a window,
+// reading x (or xs with from_xs) and writing the other; mode 0: from zero, restricting; 1: from
+// zero; 2: from the iterate plus the prolonged coarse correction, colour 1 first, with rz as in
+// launch_sweep3.
+void launch_march3(bool fp32, const LevelDesc* L, const GridState* S, JobList jl, int mode, int from_xs, int fz,
+                   hipStream_t s, int rz = 0);
+// Small-level passes: ns (1..3) red-black sweeps per launch, colour c0 first, reading x (or xs
+// with from_xs) and writing the other.  load: start from the iterate, else from zero; prolong
+// (with load): plus the coarse correction; restr: then restrict the residual (ns > 1: only
+// from zero).  bc: the plan has Dirichlet or periodic faces.
+void launch_tile(int dim, bool fp32, int bc, const LevelDesc* L, const GridState* S, JobList jl, int ns, int load,
+                 int prolong, int restr, int c0, int from_xs, hipStream_t s);
 // bc: the plan has Dirichlet or periodic faces.
 void launch_tail(int dim, bool fp32, int bc, const LevelDesc* L, const GridState* S, JobList jl, size_t smem,
                  int nu1, int nu2, int plain64, hipStream_t s);

@@ -53,8 +53,14 @@ struct DimLists {
     std::vector<HostList> sw3, sr3;            // per depth, fused 3D sweep blocks (plain / restricting)
     std::vector<int> fz_r;                     // per depth, planes per block of the restricting sweep
     std::vector<int> fz_s;                     // per depth, planes per block of the plain sweeps
+    std::vector<HostList> m3;                  // per depth, two-sweep z-march windows of fz_m3 planes
+    std::vector<int> fz_m3;                    // (0: not on this depth)
     bool fused3 = false;                       // fused 3D sweeps available (lists and xs laid out)
     int levels3 = 0;                           // leading depths that run fused sweeps
+    // small-level passes: per depth, the tiles of launches of 1, 2 and 3 sweeps (same levels as
+    // smooth); tile: available on the depths that run no marching or LDS-tile passes
+    std::vector<HostList> tl[kTileMaxNs];
+    bool tile = false;
     HostList coarsest;                         // coarsest level of grids without a tail
     HostList tail;                             // first tail level of grids with a tail
     // per depth d: the tails / coarsest levels of the grids with wide levels below d
@@ -95,12 +101,19 @@ struct Plan {
     // workspace layout (byte offsets)
     size_t off_levels = 0, off_state = 0, off_stepio = 0, off_exio = 0, off_moio = 0, off_imio = 0, off_ctrl = 0;
     size_t ws_bytes = 0;
+    // Plans whose operator differs from zero flux run the small-level passes on every depth;
+    // their levels' second iterate (xs) is the CG product vector on level 0 and, below it, the
+    // workspace's last part, from ws_core on.  A workspace that ends at ws_core is bound
+    // without it (no_xs), and the plan sweeps per colour.
+    size_t ws_core = 0;
+    bool no_xs = false;
+    size_t bound_bytes() const { return no_xs ? ws_core : ws_bytes; }
     static constexpr int kExSlots = 4;
     struct FieldOff {
         size_t x = 0, b = 0, w[3] = {0, 0, 0}, x32 = 0, b32 = 0, w32[3] = {0, 0, 0}, part = 0, scratch = 0;
         size_t X = 0, B0 = 0, R = 0, P[2] = {0, 0}, Q = 0, xs = 0;
         bool has_x = false, has_b = false, has_x32 = false, has_scratch = false, has_part = false;
-        bool has_xs = false;
+        bool has_xs = false, opt_xs = false;    // opt_xs: xs is an offset in the workspace
         bool lev0 = false, has_cg = false;
         size_t ad = 0, ad32 = 0;                // Dirichlet ghost couplings (plans with Dirichlet faces)
     };

@@ -1519,6 +1519,19 @@ __device__ __forceinline__ void unroll(F&& f) {
     }
 }
 
+// The same while more(i) holds: the first i that fails ends it.  Nested, so that no control
+// flow merges between two calls (a merge would keep every register that a skipped call
+// overwrites alive, a whole ring of planes in the marches).
+template <int I, int N, typename M, typename F>
+__device__ __forceinline__ void unroll_while(M&& more, F&& f) {
+    if constexpr (I < N) {
+        if (more(I)) {
+            f(std::integral_constant<int, I>{});
+            unroll_while<I + 1, N>(more, f);
+        }
+    }
+}
+
 // Value of v on lane l - 1 (LEFT) or l + 1 of the wavefront, 0 on lane 0 / 63: DPP
 // whole-wavefront shifts (every lane must be active).
 __device__ __forceinline__ uint32_t lane_shift(uint32_t v, bool left) {
@@ -2002,6 +2015,585 @@ k_sweep3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
                 __syncthreads();                               // shrz is reused by the next tile
             }
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Two red-black sweeps per launch of a large 3D level: the z-march of k_sweep3 with four
+// half sweeps in flight, so that a level's iterate, right-hand side and faces are read
+// once per two sweeps (a V(2,2) cycle's level pass moves 11 words a cell instead of 23, and
+// memory bandwidth bounds the single sweeps).  A workgroup owns a window of m3_px x m3_py
+// positions (32 x 16 interior columns and a halo of four), one position a thread, and
+// marches through fz planes; at step zt half sweep k updates plane zt - k.  The positions
+// of one colour class, (x + y) even or odd, belong to the first eight wavefronts, the
+// others to the last eight: in a step all four half sweeps update the same class (the
+// colour flips with both k and the plane), so half of the wavefronts do the step's
+// updates at full width while the others store the finished plane, and they swap every
+// step.  A thread keeps its position's iterate, b and lower z face for the planes in
+// flight in registers; the iterates and the x and y faces go through LDS, a ring of planes
+// stored by class so that neighbours are read at unit stride (the faces, with the column
+// and the row past the window, loaded as pairs by one class each).  One barrier a step: a
+// plane's faces are stored after it, into the slot that was last read before it.
+// Positions within k of the window's edge are wrong after k half sweeps and stay in the
+// halo (from zero the first half sweep reads no neighbour, which leaves a ring for the
+// residual).  Positions outside the level go on as their nearest one inside; the faces
+// between are zero.  Modes:
+//   M3_DOWN   from zero, and the residual restricted onto the coarse level
+//   M3_ZERO   from zero
+//   M3_UP     from the iterate plus the prolonged coarse correction, colour 1 first; with
+//             rz (level 0 under FP64 CG) also one partial of b . x per window
+// Updates and residuals have the per-colour kernels' operand order, s / dg formed by div_by
+// from the reciprocal of the position's first update, so the results are bitwise theirs.
+// What bounds it: the chain of a step's four dependent updates between two barriers (the
+// vector units are busy a third of the time, the LDS half of it); its traffic is 1.4-1.5
+// times the level's bytes (the halo's share that misses L2), 4 TB/s.  256^3, FP64 / FP32:
+// down 240 / 167 us where two single sweeps took 385 / 234 us, up 281 / 190 us against
+// 392 / 220 us.
+// ---------------------------------------------------------------------------
+enum March3Mode : int { M3_DOWN = 0, M3_ZERO = 1, M3_UP = 2 };
+
+// s / d from r = 1 / d (correctly rounded): one correction step of the quotient, exact in
+// the normal range.
+template <typename T>
+__device__ __forceinline__ T div_by(T s, T d, T r) {
+    const T q = s * r;
+    const T e = __builtin_elementwise_fma(-q, d, s);
+    return __builtin_elementwise_fma(e, r, q);
+}
+
+template <typename T>
+struct March3Slot {                                          // one plane of the ring, by class
+    static constexpr int PY = m3_py(sizeof(T)), KW = m3_px(sizeof(T)) / 2;
+    T w0[2][PY][KW];
+    T w1[2][PY + 1][KW];
+    T x[2][PY][KW];
+    T w0e[PY];                                               // the x faces of the column past the window
+};
+template <typename T, int MODE>
+struct March3Lds {
+    March3Slot<T> s[kM3R];
+    T res[2][MODE == M3_DOWN ? m3_py(sizeof(T)) : 1][m3_px(sizeof(T))];        // (also what the window's edge reads past x)
+};
+
+// A 32-bit byte offset that the compiler does not fold into a 64-bit base kept in registers.
+template <typename V, typename T>
+__device__ __forceinline__ V load_at(gptr<T> plane, uint32_t off) {
+    asm("" : "+v"(off));
+    return *(gptr<V>)((gptr<char>)plane + off);
+}
+
+template <typename T, int MODE, int CLS>
+__device__ __forceinline__ double march3_body(March3Lds<T, MODE>& t, const LevelDesc& d, const LevelDesc& cL,
+                                              int from_xs, int lt, int fz, int rz) {
+    using V2 = T __attribute__((ext_vector_type(2)));
+    using Slot = March3Slot<T>;
+    constexpr int PX = m3_px(sizeof(T)), PY = m3_py(sizeof(T)), CT = m3_class(sizeof(T));
+    constexpr int KX = PX / 2, KW = Slot::KW, H = kM3H, R = kM3R, FX = PX - 2 * H, FY = PY - 2 * H;
+    constexpr int C0 = MODE == M3_UP ? 1 : 0;
+    constexpr bool UP = MODE == M3_UP, DOWN = MODE == M3_DOWN;
+    // planes are loaded PF steps ahead (FP64 up: two would spill)
+    constexpr int PF = UP && sizeof(T) == 8 ? 1 : 2, NB = 10;
+    constexpr bool KEEP = !(UP && sizeof(T) == 8);             // reciprocals kept (else they spill)
+    const int n0 = d.n[0], n1 = d.n[1], n2 = d.n[2];           // even: the level has a coarser one
+    const int tx_n = (n0 + FX - 1) / FX, ty_n = (n1 + FY - 1) / FY;
+    const int tx = lt % tx_n, rest = lt / tx_n;
+    const int gx0 = tx * FX - H, gy0 = (rest % ty_n) * FY - H;   // even
+    const int z0 = (rest / ty_n) * fz, z1 = min(z0 + fz, n2);
+    const int zs = z0 - H, ze = z1 + H + 1 + (DOWN ? 1 : 0);
+    const long sz = (long)n0 * n1, csz = sz >> 2;
+    // the thread's position, and the pair of positions whose faces it stages: class 0 the y
+    // faces (one row more), class 1 the x faces (one pair of columns more)
+    const int m = threadIdx.x - CLS * CT;
+    const int mp = min(m, KX * PY - 1);
+    const int ly = mp / KX, kx = mp - ly * KX;
+    const int sft = (ly + CLS) & 1, lx = 2 * kx + sft;
+    const int gx = gx0 + lx, gy = gy0 + ly;
+    const bool inner = m < KX * PY && kx >= H / 2 && kx < KX - H / 2 && ly >= H && ly < PY - H && gx < n0 && gy < n1;
+    const uint32_t c = (min(max(gx, 0), n0 - 1) + min(max(gy, 0), n1 - 1) * n0) * (uint32_t)sizeof(T);
+    constexpr int KS = CLS == 0 ? KX : KX + 1, NS = CLS == 0 ? KX * (PY + 1) : (KX + 1) * PY;
+    const int ms = min(m, NS - 1);
+    const int rs = ms / KS, ks = ms - rs * KS;
+    const uint32_t cs = (min(max(gx0 + 2 * ks, 0), n0 - 2) + min(max(gy0 + rs, 0), n1 - 1) * n0) * (uint32_t)sizeof(T);
+    const bool fin = CLS == 0 ? gy0 + rs < n1 : gx0 + 2 * ks < n0;   // past the level's end: faces of weight zero
+    const uint32_t cc = ((min(max(gx, 0), n0 - 1) >> 1) + (min(max(gy, 0), n1 - 1) >> 1) * (n0 >> 1)) * (uint32_t)sizeof(T);
+    const gptr<T> xin = as_global(from_xs ? Arr<T>::xs(d) : Arr<T>::x(d));
+    const gptr<T> xout = as_global(from_xs ? Arr<T>::x(d) : Arr<T>::xs(d));
+    const gptr<T> bg = as_global(Arr<T>::b(d));
+    const gptr<T> sg = as_global(Arr<T>::w(d, CLS == 0 ? 1 : 0));
+    const gptr<T> w2g = as_global(Arr<T>::w(d, 2));
+    const gptr<T> cxg = as_global(Arr<T>::x(cL)), cbg = as_global(Arr<T>::b(cL));
+    // places in a slot, in elements: the position's own (class, row, column), shifted to its
+    // right neighbour's column, and the staged pair's two
+    constexpr int OW1 = 2 * PY * KW, OX = OW1 + 2 * (PY + 1) * KW;
+    constexpr int OTH = CLS == 0 ? PY * KW : -PY * KW;         // from the own class to the other
+    constexpr int OTH1 = CLS == 0 ? (PY + 1) * KW : -(PY + 1) * KW, OW1C = OW1 + CLS * KW;
+    const int o = (CLS * PY + ly) * KW + kx, oN = o + sft;
+    constexpr int OE = OX + 2 * PY * KW;
+    const int oR = kx + sft < KX ? oN + OTH : OE + ly;         // the right neighbour's x face
+    constexpr int SR = CLS == 0 ? PY + 1 : PY, SO = CLS == 0 ? OW1 : 0;
+    // (class 1's pair past the window has one face in use, kept apart; the other goes where
+    // it is overwritten: both values to the same place, the even one last)
+    const bool past = CLS == 1 && ks == KX;
+    const int oE = past ? OE + rs : SO + ((rs & 1) * SR + rs) * KW + ks;
+    const int oO = past ? OE + rs : SO + ((1 - (rs & 1)) * SR + rs) * KW + ks;
+    T* const base = reinterpret_cast<T*>(&t);
+    constexpr int SLOT = (int)(sizeof(Slot) / sizeof(T));
+    constexpr bool CACHE = sizeof(T) == 4;                     // in-plane faces kept from the first read
+    T X[NB], B[NB], W2[NB], RD[NB], XI[NB], C[NB], WL[NB], WR[NB], WD[NB], WU[NB];
+    V2 S[NB];
+    unroll<NB>([&](auto Qc) {
+        constexpr int q = decltype(Qc)::value;
+        X[q] = B[q] = W2[q] = RD[q] = XI[q] = C[q] = WL[q] = WR[q] = WD[q] = WU[q] = T(0);
+        S[q] = V2{T(0), T(0)};
+    });
+    auto load = [&](auto Sl, int gk) {
+        constexpr int q = decltype(Sl)::value;
+        const int kc = min(max(min(gk, z1 + H), 0), n2 - 1);
+        const long pl = kc * sz;
+        S[q] = load_at<V2>(sg + pl, cs);
+        if constexpr (UP) {
+            XI[q] = load_at<T>(xin + pl, c);
+            if constexpr (q % 2 == 0) C[q] = load_at<T>(cxg + (kc >> 1) * csz, cc);   // for two planes
+        }
+        W2[q] = load_at<T>(w2g + pl, c);
+    };
+    // (b is first used one step after its plane enters)
+    auto load_b = [&](auto Sl, int gk) {
+        constexpr int q = decltype(Sl)::value;
+        B[q] = load_at<T>(bg + min(max(min(gk, z1 + H), 0), n2 - 1) * sz, c);
+    };
+    T racc = T(0);
+    double rzacc = 0.0;
+    const int rci = m % (FX / 2), rcj = m / (FX / 2);    // coarse cell of the restriction's owners
+    const int CI = (gx0 + H) / 2 + rci, CJ = (gy0 + H) / 2 + rcj;
+    const bool rown = DOWN && CLS == 0 && m < (FX / 2) * (FY / 2) && CI < (n0 >> 1) && CJ < (n1 >> 1);
+    int s0 = 0;                                               // LDS slot of plane zt
+    auto slot = [&](int k) { return (s0 >= k ? s0 - k : s0 - k + R) * SLOT; };
+    auto step = [&](auto Qc, int zt) {
+        constexpr int q = decltype(Qc)::value;                 // register slot of plane zt; zt = q (mod 2)
+        constexpr bool ACT = ((CLS + q + C0) & 1) == 1;        // this class updates in this step
+        // plane zt enters the window
+        W2[q] = zt < n2 ? W2[q] : T(0);
+        X[q] = UP ? XI[q] + C[q - q % 2] : T(0);
+        load_b(std::integral_constant<int, (q + PF - 1) % NB>{}, zt + PF - 1);
+        load(std::integral_constant<int, (q + PF) % NB>{}, zt + PF);
+        __syncthreads();
+        {
+            // its faces and iterate (first read in the next step)
+            T* const p = base + slot(0);
+            p[oO] = fin ? S[q].y : T(0);
+            p[oE] = fin ? S[q].x : T(0);
+            if constexpr (UP) p[o + OX] = X[q];
+        }
+        if constexpr (ACT) {
+            unroll<4>([&](auto Kc) {
+                constexpr int k = decltype(Kc)::value + 1;
+                constexpr int qk = (q + NB - k) % NB, qd = (q + NB - k - 1) % NB, qu = (q + NB - k + 1) % NB;
+                T* const p = base + slot(k) + o;
+                const T* const pr = base + slot(k) + oR;
+                const T* const pn = base + slot(k) + oN;
+                if constexpr (!CACHE || k <= 2) {
+                    WL[qk] = p[0];
+                    WR[qk] = *pr;
+                    WD[qk] = p[OW1C];
+                    WU[qk] = p[OW1C + OTH1 + KW];
+                }
+                const T wl = WL[qk], wr = WR[qk], wd = WD[qk], wu = WU[qk];
+                T dg = T(1) + wl;
+                dg += wr;
+                dg += wd;
+                dg += wu;
+                dg += W2[qk];
+                dg += W2[qu];
+                if constexpr (KEEP && k <= 2) RD[qk] = T(1) / dg;
+                T s = B[qk];
+                if constexpr (UP || k > 1) {
+                    s += wl * pn[OX + OTH - 1];
+                    s += wr * pn[OX + OTH];
+                    s += wd * p[OX + OTH - KW];
+                    s += wu * p[OX + OTH + KW];
+                    s += W2[qk] * X[qd];
+                    s += W2[qu] * X[qu];
+                }
+                X[qk] = KEEP ? div_by(s, dg, RD[qk]) : s / dg;
+                p[OX] = X[qk];
+            });
+        }
+        constexpr int q4 = (q + NB - 4) % NB, q5 = (q + NB - 5) % NB, q6 = (q + NB - 6) % NB;
+        if constexpr (UP && std::is_same_v<T, double>) {
+            // (the position itself is final one step before its plane)
+            if (rz && inner && zt - 4 >= z0 && zt - 4 < z1) rzacc += B[q4] * X[q4];
+        }
+        // plane zt - 5 is final
+        const int p5 = zt - 5;
+        if (p5 >= z0 && p5 < z1) {                             // uniform
+            const T* const p = base + slot(5) + o;
+            const T* const pn = base + slot(5) + oN;
+            if constexpr (!ACT) {
+                // the resting class writes it, a pair of positions a thread
+                if (inner) {
+                    const T a = p[OX], b = p[OX + OTH];
+                    V2 o2;
+                    o2.x = sft ? b : a;
+                    o2.y = sft ? a : b;
+                    *(gptr<V2>)((gptr<char>)(xout + p5 * sz) + (c - sft * (uint32_t)sizeof(T))) = o2;
+                }
+            }
+            if constexpr (DOWN) {
+                if constexpr (!CACHE) {
+                    WL[q5] = p[0];
+                    WR[q5] = base[slot(5) + oR];
+                    WD[q5] = p[OW1C];
+                    WU[q5] = p[OW1C + OTH1 + KW];
+                }
+                const T xc = X[q5];
+                T r = B[q5] - xc;
+                r -= WL[q5] * (xc - pn[OX + OTH - 1]);
+                r -= WR[q5] * (xc - pn[OX + OTH]);
+                r -= WD[q5] * (xc - p[OX + OTH - KW]);
+                r -= WU[q5] * (xc - p[OX + OTH + KW]);
+                r -= W2[q5] * (xc - X[q6]);
+                r -= W2[q4] * (xc - X[q4]);
+                t.res[p5 & 1][ly][lx] = r;
+            }
+        }
+        if constexpr (DOWN && CLS == 0) {
+            // the owners add the residual plane of the step before (ordered by this step's barrier)
+            const int p6 = zt - 6;
+            if (p6 >= z0 && p6 < z1 && rown) {
+                const int ax = H + 2 * rci, ay = H + 2 * rcj, b = p6 & 1;
+                if (b == 0) racc = T(0);
+                racc += t.res[b][ay][ax];
+                racc += t.res[b][ay][ax + 1];
+                racc += t.res[b][ay + 1][ax];
+                racc += t.res[b][ay + 1][ax + 1];
+                if (b) {
+                    // the coarse level's sweeps start from zero (per-colour kernels read it)
+                    const uint32_t ci = CI + CJ * (n0 >> 1);
+                    (cbg + (p6 >> 1) * csz)[ci] = racc * T(0.125);
+                    (cxg + (p6 >> 1) * csz)[ci] = T(0);
+                }
+            }
+        }
+        s0 = s0 + 1 == R ? 0 : s0 + 1;
+    };
+    load(std::integral_constant<int, 0>{}, zs);
+    if constexpr (PF == 2) {
+        load_b(std::integral_constant<int, 0>{}, zs);
+        load(std::integral_constant<int, 1>{}, zs + 1);
+    }
+    int zb = zs;
+    for (; zb + NB <= ze; zb += NB) unroll<NB>([&](auto Qc) { step(Qc, zb + decltype(Qc)::value); });
+    unroll_while<0, NB - 1>([&](int i) { return zb + i < ze; },
+                            [&](auto Qc) { step(Qc, zb + decltype(Qc)::value); });
+    return rzacc;
+}
+
+template <typename T, int MODE>
+__global__ void __launch_bounds__(2 * m3_class(sizeof(T)))
+k_march3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int from_xs, int fz, int rz) {
+    __shared__ March3Lds<T, MODE> t;
+    constexpr int CT = m3_class(sizeof(T));
+    const int cls = __builtin_amdgcn_readfirstlane(threadIdx.x >= CT);
+    const XcdOrder order(jl.total);
+    for (int k = order.first(); order.more(k); k += order.per) {
+        const int tt = order.tile(k);
+        const int jb = find_job(jl.prefix, jl.njobs, tt);
+        const LevelDesc& d = L[job_level(jl, jb)];
+        if (!S[d.sidx].active) continue;                       // uniform per window
+        const LevelDesc& cL = L[d.coarse];
+        const int lt = tt - job_start(jl, jb);
+        // (both classes pass the same barriers: one a step)
+        double acc = cls == 0 ? march3_body<T, MODE, 0>(t, d, cL, from_xs, lt, fz, rz)
+                              : march3_body<T, MODE, 1>(t, d, cL, from_xs, lt, fz, rz);
+        __syncthreads();                                       // the slots are reused by the next window
+        if constexpr (MODE == M3_UP && std::is_same_v<T, double>) {
+            if (rz) {
+                double unused = 0.0;
+                block_sum2<2 * CT>(acc, unused, &t.s[0].w0[0][0][0]);
+                if (threadIdx.x == 0) d.part[lt] = acc;
+                __syncthreads();
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Small-level passes: NS whole red-black sweeps (and the prolongation before or the
+// restriction after them) of one tile per workgroup, for levels with too few cells to
+// fill the chip with marching windows, where a V-cycle costs its launches: a half sweep
+// per launch takes 4 us however few cells it has, so a 48^3 level's three sweeps and
+// restriction were seven launches.  A workgroup holds a window of kTileCells positions
+// (16^3, or 64^2 in 2D), four a thread, two of each colour: the iterate sits in LDS,
+// stored by colour (cell li of a row at li / 2), and a cell's right-hand side, its six
+// face weights (the upper ones loaded from the neighbour's slot) and diagonal in its
+// thread's registers, so a half sweep reads only neighbours' iterates, all at unit
+// stride.  Positions within k of the window's edge are wrong after k half sweeps (they
+// take whatever lies past the edge), one ring less where the sweeps start from zero: the
+// halo H covers them, and only the (P - 2H)^d interior is written.  Pairs of positions load
+// as vectors, and a wavefront's rows have one parity, so that which position of a pair takes
+// which colour is known to the whole wavefront (no selects).  What bounds it is latency: the
+// descriptor's and the operands' loads, 2 NS half sweeps with a barrier each, the stores.
+// 7.5-9.5 us for one to three sweeps of a 24^3 or 48^3 level in FP64 (6-7 us in FP32), where
+// the per-colour kernels took 25 us for three sweeps on the way up and 32 us on the way down.
+// Every update and residual has the operand order of the per-colour kernels, and s / dg is
+// formed from the kept reciprocal with one Newton correction (exact in the normal range),
+// so both paths give bitwise equal results.  BC: periodic axes wrap (the window holds
+// copies of the wrapped cells), Dirichlet couplings add to the diagonal.
+// ---------------------------------------------------------------------------
+enum TileFlag : int { TILE_LOAD = 1, TILE_PROLONG = 2, TILE_RESTR = 4 };
+
+template <int DIM>
+struct TileGeo {
+    static constexpr int P = tile_p(DIM);                      // positions per axis
+    static constexpr int KX = P / 2, SZ = KX * P;              // pairs per row and per plane
+    static constexpr int HALF = kTileCells / 2;                // pairs: cells of one colour
+    static constexpr int PAD = DIM == 3 ? SZ : KX * (P / 2);   // reads past the window's edge
+    static constexpr int RPW = 64 / KX;                        // rows a wavefront holds
+};
+
+template <typename T, int DIM, int NS>
+struct TileLds {
+    using G = TileGeo<DIM>;
+    static constexpr int FX = G::P - 2 * tile_hx(NS), F = G::P - 2 * tile_halo(NS);
+    T x[2][G::HALF + 2 * G::PAD];
+    T res[DIM == 3 ? FX * F * F : FX * F];
+};
+
+// Value i of a level array of less than 4 GB (the host sends no larger level here): a scalar
+// base and a 32-bit offset, one address instruction a load.
+template <typename V, typename T>
+__device__ __forceinline__ V small_at(gptr<T> p, uint32_t i) {
+    return *(gptr<V>)((gptr<char>)p + i * (uint32_t)sizeof(T));
+}
+
+// One tile for a wavefront whose pairs' even positions take colour PAR (0: the first colour).
+template <int DIM, typename T, int NS, bool BC, int PAR>
+__device__ __forceinline__ void tile_body(TileLds<T, DIM, NS>& t, const LevelDesc& d, const LevelDesc& cL, int flags,
+                                          int from_xs, int active, int gx0, int gy0, int gz0, int kx, int lj, int lk) {
+    using G = TileGeo<DIM>;
+    using V2 = T __attribute__((ext_vector_type(2)));
+    constexpr int P = G::P, KX = G::KX, SZ = G::SZ, PAD = G::PAD;
+    constexpr int HX = tile_hx(NS), H = tile_halo(NS), FX = TileLds<T, DIM, NS>::FX, F = TileLds<T, DIM, NS>::F;
+    constexpr int CPC = G::HALF / kTileThreads;                // pairs a thread
+    constexpr int DJ = DIM == 3 ? 0 : P / CPC, DK = DIM == 3 ? P / CPC : 0;   // from a thread's pair to its next
+    const int n0 = d.n[0], n1 = d.n[1], n2 = d.n[2];           // even: the level has a coarser one
+    const int sy = n0, sz = n0 * n1;
+    const int pm = BC ? d.per_mask : 0;
+    const bool px = BC && (pm & 1), py = BC && (pm & 2), pz = BC && (pm & 4);
+    const gptr<T> bg = as_global(Arr<T>::b(d));
+    const gptr<T> w0g = as_global(Arr<T>::w(d, 0));
+    const gptr<T> w1g = as_global(Arr<T>::w(d, 1));
+    const gptr<T> w2g = as_global(DIM == 3 ? Arr<T>::w(d, 2) : Arr<T>::w(d, 0));
+    const bool has_a = BC && Arr<T>::ad(d) != nullptr;
+    const gptr<T> ag = has_a ? as_global(Arr<T>::ad(d)) : bg;
+    // rows are stored even ones first, so that a wavefront's rows (one parity) are contiguous
+    const int mrow = (lj >> 1) + (P / 2) * (lj & 1);
+    const int m0 = kx + KX * (mrow + (DIM == 3 ? P * lk : 0));
+    const int up = lj & 1 ? -KX * (P / 2 - 1) : KX * (P / 2);  // to the row above, and below
+    const int dn = lj & 1 ? -KX * (P / 2) : KX * (P / 2 - 1);
+    constexpr int DM = DIM == 3 ? P / CPC * SZ : KX * (P / 2) / CPC;
+    // positions outside the level read the nearest pair inside and go on as that (they are
+    // no neighbour of a cell inside: the faces between are zero); periodic axes wrap
+    auto place = [&](int v, int n, bool per, int last) {
+        if (BC && per) {
+            v %= n;
+            return v + (v < 0 ? n : 0);
+        }
+        return min(max(v, 0), n - last);
+    };
+    // colour q of a pair sits at its odd position where PAR != q
+    T b[2][CPC], wl[2][CPC], wr[2][CPC], wd[2][CPC], wu[2][CPC], wb[2][CPC], wf[2][CPC], ar[2][CPC], xv[2][CPC];
+    const int i = place(gx0 + 2 * kx, n0, px, 2);
+    uint32_t at[CPC], atc[CPC];
+    V2 vb[CPC], v0[CPC], v1[CPC], v1u[CPC], v2[CPC], v2f[CPC], va[CPC], x2[CPC];
+    T v0r[CPC], xc[CPC];
+    bool uin[CPC], fin[CPC];
+    const bool rin = i + 2 < n0 || px;
+#pragma unroll
+    for (int u = 0; u < CPC; ++u) {
+        const int j = place(gy0 + lj + u * DJ, n1, py, 1);
+        const int k = DIM == 3 ? place(gz0 + lk + u * DK, n2, pz, 1) : 0;
+        uin[u] = j + 1 < n1 || py;
+        fin[u] = DIM == 3 && (k + 1 < n2 || pz);
+        const uint32_t idx = i + sy * j + (DIM == 3 ? sz * k : 0);
+        at[u] = idx;
+        atc[u] = (i >> 1) + (n0 >> 1) * ((j >> 1) + (DIM == 3 ? (n1 >> 1) * (k >> 1) : 0));
+        // the face above a pair is its upper neighbour's lower one
+        vb[u] = small_at<V2>(bg, idx);
+        v0[u] = small_at<V2>(w0g, idx);
+        v0r[u] = small_at<T>(w0g, i + 2 < n0 ? idx + 2 : (px ? idx - (n0 - 2) : idx));
+        v1[u] = small_at<V2>(w1g, idx);
+        v1u[u] = small_at<V2>(w1g, j + 1 < n1 ? idx + sy : (py ? idx - (n1 - 1) * sy : idx));
+        if (DIM == 3) {
+            v2[u] = small_at<V2>(w2g, idx);
+            v2f[u] = small_at<V2>(w2g, k + 1 < n2 ? idx + sz : (pz ? idx - (n2 - 1) * sz : idx));
+        }
+        if (BC) va[u] = small_at<V2>(ag, idx);
+    }
+    const gptr<T> cx = as_global(Arr<T>::x(cL));
+    if (flags & TILE_LOAD) {
+        const gptr<T> xin = as_global(from_xs ? Arr<T>::xs(d) : Arr<T>::x(d));
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            x2[u] = small_at<V2>(xin, at[u]);
+            xc[u] = flags & TILE_PROLONG ? small_at<T>(cx, atc[u]) : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            if (flags & TILE_PROLONG) x2[u] += xc[u];
+            xv[PAR][u] = x2[u].x;
+            xv[1 - PAR][u] = x2[u].y;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) xv[0][u] = xv[1][u] = T(0);
+    }
+    if (!active) return;                                       // uniform per tile
+    if (threadIdx.x < PAD) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            t.x[q][threadIdx.x] = T(0);
+            t.x[q][PAD + G::HALF + threadIdx.x] = T(0);
+        }
+    }
+    T dg[2][CPC], rd[2][CPC];
+#pragma unroll
+    for (int u = 0; u < CPC; ++u) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bool odd = PAR != q;
+            b[q][u] = odd ? vb[u].y : vb[u].x;
+            wl[q][u] = odd ? v0[u].y : v0[u].x;
+            wr[q][u] = odd ? (rin ? v0r[u] : T(0)) : v0[u].y;
+            wd[q][u] = odd ? v1[u].y : v1[u].x;
+            wu[q][u] = uin[u] ? (odd ? v1u[u].y : v1u[u].x) : T(0);
+            if (DIM == 3) {
+                wb[q][u] = odd ? v2[u].y : v2[u].x;
+                wf[q][u] = fin[u] ? (odd ? v2f[u].y : v2f[u].x) : T(0);
+            }
+            if (BC) ar[q][u] = odd ? va[u].y : va[u].x;
+            T g = T(1) + wl[q][u];
+            g += wr[q][u];
+            g += wd[q][u];
+            g += wu[q][u];
+            if (DIM == 3) {
+                g += wb[q][u];
+                g += wf[q][u];
+            }
+            if (BC && has_a) g += ar[q][u];
+            dg[q][u] = g;
+            rd[q][u] = T(1) / g;
+            t.x[q][PAD + m0 + u * DM] = xv[q][u];
+        }
+    }
+    __syncthreads();
+    for (int it = 0; it < NS; ++it) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            constexpr int sft0 = PAR;                          // colour 0 at position 2 kx + PAR
+            const int sft = q ? 1 - sft0 : sft0;
+#pragma unroll
+            for (int u = 0; u < CPC; ++u) {
+                const T* o = &t.x[1 - q][PAD + m0 + u * DM];
+                T s = b[q][u];
+                s += wl[q][u] * o[sft - 1];
+                s += wr[q][u] * o[sft];
+                s += wd[q][u] * o[dn];
+                s += wu[q][u] * o[up];
+                if (DIM == 3) {
+                    s += wb[q][u] * o[-SZ];
+                    s += wf[q][u] * o[SZ];
+                }
+                t.x[q][PAD + m0 + u * DM] = div_by(s, dg[q][u], rd[q][u]);
+            }
+            __syncthreads();
+        }
+    }
+    const gptr<T> xout = as_global(from_xs ? Arr<T>::x(d) : Arr<T>::xs(d));
+    const bool restr = flags & TILE_RESTR;
+    const int ie = 2 * kx - HX;
+#pragma unroll
+    for (int u = 0; u < CPC; ++u) {
+        const int jj = lj + u * DJ - H, zz = DIM == 3 ? lk + u * DK - H : 0;
+        if (ie < 0 || ie >= FX || jj < 0 || jj >= F || zz < 0 || zz >= F) continue;
+        const T xe = t.x[PAR][PAD + m0 + u * DM], xo = t.x[1 - PAR][PAD + m0 + u * DM];
+        const int gi = gx0 + 2 * kx, gj = gy0 + lj + u * DJ, gk = gz0 + lk + u * DK;
+        if (gi < n0 && gj < n1 && gk < n2) {
+            V2 o2;
+            o2.x = xe;
+            o2.y = xo;
+            *(gptr<V2>)(xout + at[u]) = o2;
+        }
+        if (restr) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                constexpr int sft0 = PAR;
+                const int sft = q ? 1 - sft0 : sft0;
+                const T c = q == PAR ? xe : xo;
+                const T* o = &t.x[1 - q][PAD + m0 + u * DM];
+                T r = b[q][u] - c;
+                r -= wl[q][u] * (c - o[sft - 1]);
+                r -= wr[q][u] * (c - o[sft]);
+                r -= wd[q][u] * (c - o[dn]);
+                r -= wu[q][u] * (c - o[up]);
+                if (DIM == 3) {
+                    r -= wb[q][u] * (c - o[-SZ]);
+                    r -= wf[q][u] * (c - o[SZ]);
+                }
+                if (BC && has_a) r -= ar[q][u] * c;
+                t.res[ie + sft + FX * (jj + F * zz)] = r;
+            }
+        }
+    }
+}
+
+template <int DIM, typename T, int NS, bool BC>
+__global__ void __launch_bounds__(kTileThreads)
+k_tile(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int flags, int c0, int from_xs) {
+    using G = TileGeo<DIM>;
+    constexpr int HX = tile_hx(NS), H = tile_halo(NS), FX = TileLds<T, DIM, NS>::FX, F = TileLds<T, DIM, NS>::F;
+    __shared__ TileLds<T, DIM, NS> t;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // a wavefront's first pairs: rows of one parity (and, in 3D, of one plane)
+    const int kx = lane % G::KX;
+    const int lj = 2 * (lane / G::KX + (DIM == 3 ? 0 : G::RPW * (wave >> 1))) + (wave & 1);
+    const int lk = DIM == 3 ? wave >> 1 : 0;
+    const XcdOrder order(jl.total);
+    for (int kk = order.first(); order.more(kk); kk += order.per) {
+        const int tt = order.tile(kk);
+        const int jb = find_job(jl.prefix, jl.njobs, tt);
+        const LevelDesc& d = L[job_level(jl, jb)];
+        const LevelDesc& cL = L[d.coarse];
+        const int active = S[d.sidx].active;
+        const int lt = tt - job_start(jl, jb);
+        const int tx_n = (d.n[0] + FX - 1) / FX, ty_n = (d.n[1] + F - 1) / F;
+        const int tx = lt % tx_n, rest = lt / tx_n;
+        const int gx0 = tx * FX - HX, gy0 = (rest % ty_n) * F - H, gz0 = DIM == 3 ? (rest / ty_n) * F - H : 0;
+        // the colour of its pairs' even positions, counted from the pass's first colour
+        const int par = (gx0 + gy0 + gz0 + (wave & 1) + lk + c0) & 1;
+        if (par) tile_body<DIM, T, NS, BC, 1>(t, d, cL, flags, from_xs, active, gx0, gy0, gz0, kx, lj, lk);
+        else tile_body<DIM, T, NS, BC, 0>(t, d, cL, flags, from_xs, active, gx0, gy0, gz0, kx, lj, lk);
+        if (!active) continue;                                 // uniform per tile
+        if (flags & TILE_RESTR) {
+            __syncthreads();
+            const gptr<T> cx = as_global(Arr<T>::x(cL)), cb = as_global(Arr<T>::b(cL));
+            const int cn0 = cL.n[0], cn1 = cL.n[1], cn2 = cL.n[2];
+            constexpr int FCX = FX / 2, FC = F / 2, NC = DIM == 3 ? FCX * FC * FC : FCX * FC;
+            for (int e = threadIdx.x; e < NC; e += kTileThreads) {
+                const int ci = e % FCX, cj = (e / FCX) % FC, ck = DIM == 3 ? e / (FCX * FC) : 0;
+                const int I = (gx0 + HX) / 2 + ci, J = (gy0 + H) / 2 + cj, K = DIM == 3 ? (gz0 + H) / 2 + ck : 0;
+                if (I >= cn0 || J >= cn1 || K >= cn2) continue;
+                T s = T(0);
+#pragma unroll
+                for (int c = 0; c < (1 << DIM); ++c)
+                    s += t.res[2 * ci + (c & 1) + FX * (2 * cj + ((c >> 1) & 1) + F * (DIM == 3 ? 2 * ck + (c >> 2) : 0))];
+                const int cidx = I + cn0 * (J + (DIM == 3 ? cn1 * K : 0));
+                cb[cidx] = s * T(DIM == 3 ? 0.125 : 0.25);
+                cx[cidx] = T(0);                               // per-colour sweeps below start from it
+            }
+        }
+        __syncthreads();                                       // the window is reused by the next tile
     }
 }
 
@@ -3314,6 +3906,45 @@ void launch_march2(bool fp32, const LevelDesc* L, const GridState* S, JobList jl
         else { if (fp32) FLD_MARCH(float, false, true); else FLD_MARCH(double, false, true); }
     });
 #undef FLD_MARCH
+}
+
+void launch_march3(bool fp32, const LevelDesc* L, const GridState* S, JobList jl, int mode, int from_xs, int fz,
+                   hipStream_t s, int rz) {
+    if (jl.total <= 0) return;
+    // b and three face arrays read, the iterate read (up) and written; the coarse b and x
+    // written (down), the coarse correction read (up)
+    const double words = mode == M3_DOWN ? 5.0 + 2.0 / 8.0 : (mode == M3_ZERO ? 5.0 : 6.0 + 1.0 / 8.0);
+    if (acct_add(jl.cells * (fp32 ? 4.0 : 8.0) * words)) return;
+    const int g = blocks_for_xcd(jl.total, jl.total);          // one window a workgroup
+#define FLD_MARCH3(M_)                                                                                              \
+    do {                                                                                                           \
+        if (fp32) hipLaunchKernelGGL((k_march3<float, M_>), dim3(g), dim3(2 * m3_class(4)), 0, s, L, S, jl, from_xs, fz, rz);   \
+        else hipLaunchKernelGGL((k_march3<double, M_>), dim3(g), dim3(2 * m3_class(8)), 0, s, L, S, jl, from_xs, fz, rz);       \
+    } while (0)
+    if (mode == M3_DOWN) FLD_MARCH3(M3_DOWN);
+    else if (mode == M3_ZERO) FLD_MARCH3(M3_ZERO);
+    else FLD_MARCH3(M3_UP);
+#undef FLD_MARCH3
+}
+
+void launch_tile(int dim, bool fp32, int bc, const LevelDesc* L, const GridState* S, JobList jl, int ns, int load,
+                 int prolong, int restr, int c0, int from_xs, hipStream_t s) {
+    if (jl.total <= 0) return;
+    // b and the face arrays read, the iterate read (not from zero) and written; the coarse
+    // correction read, or the coarse b and x written
+    const double words = 2.0 + dim + (load ? 1.0 : 0.0) + (prolong ? 1.0 : 0.0) / (1 << dim) +
+                         (restr ? 2.0 : 0.0) / (1 << dim);
+    if (acct_add(jl.cells * (fp32 ? 4.0 : 8.0) * words)) return;
+    const int flags = (load ? TILE_LOAD : 0) | (prolong ? TILE_PROLONG : 0) | (restr ? TILE_RESTR : 0);
+    const int g = blocks_for_xcd(jl.total, jl.total);          // one tile a workgroup
+#define FLD_TILE(T_, NS_, B_) hipLaunchKernelGGL((k_tile<D, T_, NS_, B_>), dim3(g), dim3(kTileThreads), 0, s, L, S, jl, flags, c0, from_xs)
+#define FLD_TILE_NS(T_, B_) do { if (ns == 1) FLD_TILE(T_, 1, B_); else if (ns == 2) FLD_TILE(T_, 2, B_); else FLD_TILE(T_, 3, B_); } while (0)
+    FLD_DISPATCH_DIM(dim, {
+        if (bc) { if (fp32) FLD_TILE_NS(float, true); else FLD_TILE_NS(double, true); }
+        else { if (fp32) FLD_TILE_NS(float, false); else FLD_TILE_NS(double, false); }
+    });
+#undef FLD_TILE_NS
+#undef FLD_TILE
 }
 
 template <int DIM, typename T, bool BC>

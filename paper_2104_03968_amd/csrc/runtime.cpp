@@ -156,6 +156,23 @@ void finish_fused(const Plan& p, DimLists& D) {
                 if (rounds(a, false, fz) < rounds(a, false, D.fz_s[dpt])) D.fz_s[dpt] = fz;
         for (int fz : {8, 16, 32, 64})
             if (rounds(r, true, fz) < rounds(r, true, D.fz_r[dpt])) D.fz_r[dpt] = fz;
+        // two-sweep windows: the plane depth of fewest block steps (fz and nine more); a plane
+        // has to stay below 4 GB (32-bit offsets)
+        HostList& m = D.m3[dpt];
+        const int word = p.mixed ? 4 : 8;
+        int64_t best = -1;
+        D.fz_m3[dpt] = 0;
+        bool fits = true;
+        for (int32_t li : m.levels) fits = fits && (int64_t)p.levels[li].n[0] * p.levels[li].n[1] <= (1 << 28);
+        for (int fz : {4, 8, 16, 32, 64}) {
+            int64_t tiles = 0;
+            for (int32_t li : m.levels) tiles += march3_tiles(p.levels[li].n, word, fz);
+            const int64_t cost = ((tiles + p.ncu - 1) / p.ncu) * (fz + 9);
+            if (fits && (best < 0 || cost < best)) { best = cost; D.fz_m3[dpt] = fz; }
+        }
+        m.prefix.assign(1, 0);
+        for (int32_t li : m.levels)
+            m.prefix.push_back(m.prefix.back() + march3_tiles(p.levels[li].n, word, D.fz_m3[dpt] ? D.fz_m3[dpt] : 64));
         a.prefix.assign(1, 0);
         r.prefix.assign(1, 0);
         for (int32_t li : a.levels)
@@ -163,10 +180,15 @@ void finish_fused(const Plan& p, DimLists& D) {
         for (int32_t li : r.levels)
             r.prefix.push_back(r.prefix.back() + sweep3_tiles(p.levels[li].n, true, D.fz_r[dpt]));
     }
-    // a fused sweep marches through its planes in sequence, so a level needs many blocks
-    // to fill the chip: by default only the leading depths whose plain sweep has at least
-    // one block per two compute units run fused, the coarser ones per colour (at 256^3 the
-    // two finest, as the autotuner also picks)
+    // A marching sweep walks its planes in sequence, so small levels run the small-level passes
+    // instead: by default from the depth on whose two-sweep tiles run at once (one a compute
+    // unit).  48^3 (216 tiles): 8.7 us for two sweeps against 11.5 us marching; 64^3 (512 tiles,
+    // two rounds): 15 us against 11.5 us.
+    auto tiles2 = [&](const std::vector<int32_t>& levels) {
+        int64_t n = 0;
+        for (int32_t li : levels) n += tile_tiles(p.levels[li].n, 3, 2);
+        return n;
+    };
     // the last level-0 up sweep under FP64 CG also forms r . z; it marches a fixed plane
     // depth, so a grid's partials (one per window) do not depend on the tuned one
     D.rz3.levels = D.sw3.empty() ? std::vector<int32_t>{} : D.sw3[0].levels;
@@ -178,7 +200,7 @@ void finish_fused(const Plan& p, DimLists& D) {
         D.levels3 = std::min(p.sweep3_levels, nd);
     } else {
         D.levels3 = 0;
-        while (D.levels3 < nd && 2 * D.sw3[D.levels3].prefix.back() >= p.ncu) ++D.levels3;
+        while (D.levels3 < nd && tiles2(D.sw3[D.levels3].levels) > p.ncu) ++D.levels3;
     }
     D.thr_dn.assign(D.down2.size(), kBlock);
     D.thr_up.assign(D.up2.size(), kBlock);
@@ -422,11 +444,28 @@ static void build_lists(Plan& p) {
                    (p.nuc1 + p.nuc2) % 2 == 0;
         D.sw3.resize(D.fused3 ? maxdepth : 0);
         D.sr3.resize(D.fused3 ? maxdepth : 0);
+        D.m3.resize(D.fused3 ? maxdepth : 0);
+        D.fz_m3.assign(D.m3.size(), 0);
         for (int dpt = 0; dpt < (int)D.sw3.size(); ++dpt) {
             D.sw3[dpt].levels = D.smooth[dpt].levels;
             D.sr3[dpt].levels = D.smooth[dpt].levels;
+            D.m3[dpt].levels = D.smooth[dpt].levels;
         }
         finish_fused(p, D);
+        // The small-level passes take the depths that no other fused pass does: in 3D those
+        // past the sweeps' leading depths, and every depth of a plan whose operator differs
+        // from zero flux (conjugate gradients only: their second iterate on level 0 is the
+        // CG product vector).  They alternate between x and xs.
+        D.tile = maxdepth > 0 && ((D.dim == 3 && D.fused3) || (p.nb_bc() && p.krylov && p.opts.fused));
+        for (int ns = 1; ns <= kTileMaxNs; ++ns) {
+            D.tl[ns - 1].assign(D.tile ? maxdepth : 0, HostList{});
+            for (int dpt = 0; dpt < (int)D.tl[ns - 1].size(); ++dpt) {
+                HostList& l = D.tl[ns - 1][dpt];
+                l.levels = D.smooth[dpt].levels;
+                l.prefix.assign(1, 0);
+                for (int32_t li : l.levels) l.prefix.push_back(l.prefix.back() + tile_tiles(p.levels[li].n, D.dim, ns));
+            }
+        }
         for (int dpt = 0; dpt < maxdepth; ++dpt) {
             finish_list(D.smooth[dpt], p.levels, tiles_smooth);
             finish_list(D.prolong[dpt], p.levels, tiles_cell);
@@ -541,6 +580,9 @@ static void layout(Plan& p) {
         for (auto& l : D.mup) place_list(l);
         for (auto& l : D.sw3) place_list(l);
         for (auto& l : D.sr3) place_list(l);
+        for (auto& l : D.m3) place_list(l);
+        for (auto& t : D.tl)
+            for (auto& l : t) place_list(l);
         for (auto& l : D.smooth) place_list(l);
         for (auto& l : D.restrict_) place_list(l);
         for (auto& l : D.prolong) place_list(l);
@@ -614,7 +656,77 @@ static void layout(Plan& p) {
         p.field_off[g] = off;
         if (p.field_base.empty()) off = align_up(off + p.field_bytes[g]);
     }
+    p.ws_core = off;
+    for (size_t li = 0; li < NL; ++li) {
+        const LevelDesc& d = p.levels[li];
+        if (!p.nb_bc() || !p.dl[d.ndim - 2].tile || d.coarse < 0) continue;
+        p.foff[li].opt_xs = true;
+        if (d.level == 0) continue;
+        p.foff[li].xs = off;
+        off = align_up(off + (size_t)d.n[0] * d.n[1] * d.n[2] * (p.mixed ? 4 : 8));
+    }
     p.ws_bytes = off;
+}
+
+// The launches of a depth's marching sweeps: two sweeps from zero first on the way down, two
+// with the prolongation first on the way up, the others one each; the last down launch
+// restricts.  Their number has to be even (the depth's result ends in x): an odd one takes
+// the way up's pair apart.  (nu1 + nu2 is even, so single sweeps always end in x.)
+struct SweepPlan {
+    int ndown, nup;
+    bool down2, up2;
+};
+
+static SweepPlan sweep_plan(const DimLists& D, int d, int nu1, int nu2, bool load) {
+    SweepPlan t;
+    t.down2 = D.fz_m3[d] > 0 && nu1 >= 2 && !load;
+    t.up2 = D.fz_m3[d] > 0 && nu2 >= 2;
+    if (t.down2 != t.up2) t.down2 = t.up2 = false;
+    t.ndown = nu1 - (t.down2 ? 1 : 0);
+    t.nup = nu2 - (t.up2 ? 1 : 0);
+    return t;
+}
+
+// The launches of a depth's small-level passes: sweeps per launch, down then up.  A launch takes
+// up to kTileMaxNs sweeps where its tiles (of a small interior) still run at once, else two;
+// the last down launch restricts, which more than one sweep does only from zero.  Launches
+// alternate between x and xs and the depth's result ends in x, so their number is even.
+struct TilePlan {
+    std::vector<int> down, up;
+};
+
+static bool tile_plan(const Plan& p, const DimLists& D, int d, int nu1, int nu2, bool load, TilePlan& t) {
+    if (!D.tile || (p.nb_bc() && p.no_xs) || nu1 < 1 || nu2 < 1) return false;
+    // (the window's halo is read eight times over in 3D: past four rounds of tiles the
+    // per-colour kernels are faster, 40-47 us against 50-55 us for two sweeps of 96^3)
+    if (D.tl[1][d].prefix.back() > 4 * p.ncu) return false;
+    const int most = D.tl[2][d].prefix.back() <= p.ncu ? 3 : 2;
+    t = TilePlan{};
+    auto split = [&](std::vector<int>& v, int n) {
+        for (; n > 0; n -= v.back()) v.push_back(std::min(n, most));
+    };
+    if (nu1 <= most && !load) {
+        t.down.push_back(nu1);
+    } else {
+        split(t.down, nu1 - 1);
+        t.down.push_back(1);
+    }
+    split(t.up, nu2);
+    if ((t.down.size() + t.up.size()) % 2) {
+        // one launch more: take the last of several sweeps of an up launch apart, or of a
+        // down launch before the last
+        for (auto* v : {&t.up, &t.down}) {
+            const size_t n = v == &t.up ? v->size() : v->size() - 1;
+            for (size_t i = 0; i < n; ++i)
+                if ((*v)[i] > 1) {
+                    (*v)[i] -= 1;
+                    v->insert(v->begin() + i + 1, 1);
+                    return true;
+                }
+        }
+        return false;
+    }
+    return true;
 }
 
 // The multigrid part of one V-cycle of one dimension's grids (FP64 mode: on the
@@ -628,20 +740,23 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
     const bool f32 = p.mixed;
     const int plain64 = (!p.krylov && !p.mixed) ? 1 : 0;   // level-0 V-cycle starts from the iterate
     const int dim = D.dim;
-    // fused 3D sweeps on the leading depths: sweep k of a level's V-cycle (1-based)
-    // reads x and writes xs when k is odd, the reverse when k is even; nu1 + nu2 is
-    // even, so the level's result ends in x
+    // fused 3D sweeps on the leading depths: launch k of a level's V-cycle (from 0) reads x
+    // and writes xs when k is even, the reverse when k is odd; their number is even, so the
+    // level's result ends in x
     const int L3 = (D.fused3 && p.sweep3) ? D.levels3 : 0;
 
     for (int d = d0; d < D.maxdepth; ++d) {
         const int nu1 = d == 0 ? p.opts.nu1 : p.nuc1;
         if (d < L3) {
-            for (int k = 1; k <= nu1; ++k) {
-                const bool load = k > 1 || (d == d0 && load0);
-                const bool restr = k == nu1;
-                const int mode = restr ? (load ? 2 : 3) : (load ? 0 : 1);
-                launch_sweep3(f32, p.dL, p.dS, restr ? D.sr3[d].dev : D.sw3[d].dev, mode, 0, k % 2 == 0,
-                              restr ? D.fz_r[d] : D.fz_s[d], p.nblk, s);
+            const SweepPlan t = sweep_plan(D, d, nu1, d == 0 ? p.opts.nu2 : p.nuc2, d == d0 && load0);
+            for (int k = 0; k < t.ndown; ++k) {
+                const bool load = k > 0 || (d == d0 && load0), restr = k + 1 == t.ndown;
+                if (k == 0 && t.down2)
+                    launch_march3(f32, p.dL, p.dS, D.m3[d].dev, restr ? 0 : 1, 0, D.fz_m3[d], s);
+                else
+                    launch_sweep3(f32, p.dL, p.dS, restr ? D.sr3[d].dev : D.sw3[d].dev,
+                                  restr ? (load ? 2 : 3) : (load ? 0 : 1), 0, k % 2, restr ? D.fz_r[d] : D.fz_s[d],
+                                  p.nblk, s);
             }
             continue;
         }
@@ -652,6 +767,12 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
         if (D.fused) {
             launch_down2(f32, p.dL, p.dS, D.down2[d].dev, nu1, d == d0 ? load0 : 0, p.tile_wide,
                          d == 0 ? p.tile_rows : p.tile_rows_c, D.thr_dn[d], p.nblk, s);
+            continue;
+        }
+        if (TilePlan t; tile_plan(p, D, d, nu1, d == 0 ? p.opts.nu2 : p.nuc2, d == d0 && load0, t)) {
+            for (size_t k = 0; k < t.down.size(); ++k)
+                launch_tile(dim, f32, p.nb_bc(), p.dL, p.dS, D.tl[t.down[k] - 1][d].dev, t.down[k],
+                            k > 0 || (d == d0 && load0), 0, k + 1 == t.down.size(), 0, k % 2, s);
             continue;
         }
         for (int it = 0; it < nu1; ++it) {
@@ -666,11 +787,15 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
     for (int d = D.maxdepth - 1; d >= d0; --d) {
         const int nu1 = d == 0 ? p.opts.nu1 : p.nuc1, nu2 = d == 0 ? p.opts.nu2 : p.nuc2;
         if (d < L3) {
-            for (int k = nu1 + 1; k <= nu1 + nu2; ++k) {
-                const int mode = k == nu1 + 1 ? 4 : 0;
-                const bool rz = rz0 && d == 0 && k == nu1 + nu2 && mode == 0;
-                launch_sweep3(f32, p.dL, p.dS, rz ? D.rz3.dev : D.sw3[d].dev, mode, 1, k % 2 == 0,
-                              rz ? kRz3Fz : D.fz_s[d], p.nblk, s, rz ? 1 : 0);
+            const SweepPlan t = sweep_plan(D, d, nu1, nu2, d == d0 && load0);
+            for (int k = 0; k < t.nup; ++k) {
+                const bool rz = rz0 && d == 0 && k + 1 == t.nup;
+                const int from_xs = (t.ndown + k) % 2;
+                if (k == 0 && t.up2)
+                    launch_march3(f32, p.dL, p.dS, D.m3[d].dev, 2, from_xs, D.fz_m3[d], s, rz);
+                else
+                    launch_sweep3(f32, p.dL, p.dS, rz ? D.rz3.dev : D.sw3[d].dev, k == 0 ? 4 : 0, 1, from_xs,
+                                  rz ? kRz3Fz : D.fz_s[d], p.nblk, s, rz);
             }
             continue;
         }
@@ -681,6 +806,12 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
         if (D.fused) {
             launch_up2(f32, p.dL, p.dS, D.up2[d].dev, nu2, p.tile_wide, d == 0 ? p.tile_rows_u : p.tile_rows_c,
                        D.thr_up[d], p.nblk, s);
+            continue;
+        }
+        if (TilePlan t; tile_plan(p, D, d, nu1, nu2, d == d0 && load0, t)) {
+            for (size_t k = 0; k < t.up.size(); ++k)
+                launch_tile(dim, f32, p.nb_bc(), p.dL, p.dS, D.tl[t.up[k] - 1][d].dev, t.up[k], 1, k == 0, 0, 1,
+                            (t.down.size() + k) % 2, s);
             continue;
         }
         launch_prolong(dim, f32, p.dL, p.dS, D.prolong[d].dev, p.nblk, s);
@@ -694,6 +825,10 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
 // Whether the first smoothing kernel of level 0 in a V-cycle reads the iterate (the
 // per-colour kernels do; fused sweeps from zero and the fused 2D down pass do not).
 static bool level0_reads_iterate(const Plan& p, const DimLists& D) {
+    // (a grid without a coarse level is solved from the stored iterate, which has to be zero)
+    if (TilePlan t; D.tile && D.smooth[0].levels.size() == D.l0_cell.levels.size() &&
+                    tile_plan(p, D, 0, p.opts.nu1, p.opts.nu2, false, t))
+        return false;
     if (D.dim == 3) return !(D.fused3 && p.sweep3 && D.levels3 >= 1);
     return !D.fused;
 }
@@ -716,7 +851,11 @@ static bool rz_in_march(const Plan& p, const DimLists& D) {
     return D.fused && !D.march.empty() && D.march[0] && D.mfz[0] == kMarchFz &&
            D.mup[0].levels.size() == D.l0_cell.levels.size();
 }
-static const JobList& rz_list(const DimLists& D) { return D.dim == 3 ? D.rz3.dev : D.mup[0].dev; }
+static const JobList& rz_list(const Plan& p, const DimLists& D) {
+    if (D.dim == 2) return D.mup[0].dev;
+    const SweepPlan t = sweep_plan(D, 0, p.opts.nu1, p.opts.nu2, false);
+    return t.up2 && t.nup == 1 ? D.m3[0].dev : D.rz3.dev;
+}
 
 // Full-multigrid cycle on the V-cycle's level-0 arrays (Sec. 3.4 starts each solve
 // with one): the right-hand side averaged down to every grid's deepest wide level,
@@ -777,7 +916,7 @@ static void enqueue_cycle(Plan& p, hipStream_t s) {
             // next kernel's blocks (D.fold), or in a k_finalize launch
             const bool fin_launch = !ff && !D.fold;
             if (rzm) {
-                launch_finalize(p.dL, p.dS, rz_list(D), FIN_RZ, rt, mc, s);
+                launch_finalize(p.dL, p.dS, rz_list(p, D), FIN_RZ, rt, mc, s);
             } else {
                 launch_cg_rz(dim, p.mixed, p.dL, p.dS, l0, ff ? FIN_RZ : -1, rt, mc, cell_blocks(p), s);
                 if (fin_launch) launch_finalize(p.dL, p.dS, l0, FIN_RZ, rt, mc, s);
@@ -870,6 +1009,7 @@ int plan_set_shape(Plan& p, const LaunchShape& sh) {
         for (auto& l : D.up2) if ((rc = upload_list(p, l)) != FLD_OK) return rc;
         for (auto& l : D.sw3) if ((rc = upload_list(p, l)) != FLD_OK) return rc;
         for (auto& l : D.sr3) if ((rc = upload_list(p, l)) != FLD_OK) return rc;
+        for (auto& l : D.m3) if ((rc = upload_list(p, l)) != FLD_OK) return rc;
     }
     return FLD_OK;
 }
@@ -887,7 +1027,8 @@ static void stage_list(Plan& p, HostList& l, char* img) {
 
 int plan_bind(Plan& p, void* dev, size_t bytes, const GridState* init) {
     if (!dev) return FLD_ERR_INVALID_ARG;
-    if (bytes < p.ws_bytes) return FLD_ERR_NO_WORKSPACE;
+    if (bytes < p.ws_core) return FLD_ERR_NO_WORKSPACE;
+    p.no_xs = bytes < p.ws_bytes;
     if ((reinterpret_cast<uintptr_t>(dev) % kAlign) != 0) return FLD_ERR_INVALID_ARG;
     p.ws = static_cast<char*>(dev);
     char* const tab = p.ws;
@@ -921,6 +1062,11 @@ int plan_bind(Plan& p, void* dev, size_t bytes, const GridState* init) {
         d.Q = dp(f.Q, f.has_cg);
         d.xs = (f.has_xs && !p.mixed) ? reinterpret_cast<double*>(ws + f.xs) : nullptr;
         d.xs32 = (f.has_xs && p.mixed) ? reinterpret_cast<float*>(ws + f.xs) : nullptr;
+        if (f.opt_xs && !p.no_xs) {
+            char* const xs = d.level == 0 ? reinterpret_cast<char*>(d.Q) : p.ws + f.xs;
+            if (p.mixed) d.xs32 = reinterpret_cast<float*>(xs);
+            else d.xs = reinterpret_cast<double*>(xs);
+        }
         d.ad = p.has_dir ? reinterpret_cast<double*>(ws + f.ad) : nullptr;
         d.ad32 = (p.has_dir && p.mixed) ? reinterpret_cast<float*>(ws + f.ad32) : nullptr;
         d.sidx = p.ext_state ? p.grid_slot[d.grid] : d.grid;
@@ -954,8 +1100,8 @@ int plan_bind(Plan& p, void* dev, size_t bytes, const GridState* init) {
         stage_list(p, D.rz3, img);
         stage_list(p, D.coarsest, img);
         stage_list(p, D.tail, img);
-        for (auto* v : {&D.coarsen, &D.down2, &D.up2, &D.mdn, &D.mup, &D.sw3, &D.sr3, &D.smooth, &D.restrict_,
-                        &D.prolong, &D.tail_from, &D.coarsest_from})
+        for (auto* v : {&D.coarsen, &D.down2, &D.up2, &D.mdn, &D.mup, &D.sw3, &D.sr3, &D.m3, &D.tl[0], &D.tl[1], &D.tl[2],
+                        &D.smooth, &D.restrict_, &D.prolong, &D.tail_from, &D.coarsest_from})
             for (auto& l : *v) stage_list(p, l, img);
         if (!D.tail.empty() && prepare_tail(D.dim, p.mixed, D.tail_smem) != 0) {
             g_last_error = "hipFuncSetAttribute(max dynamic LDS) failed for the tail kernel";
@@ -1116,7 +1262,7 @@ static int step(Plan& p, const double* const* E_in, const double* const* kr, dou
 int plan_step_noalloc(Plan& p, void* dev, size_t bytes, const double* const* E_in, const double* const* kr,
                       double* const* E_out, const double* dt, hipStream_t s, fld_stats* stats) {
     if (p.ws) return FLD_ERR_INVALID_ARG;                 // bound to a caller workspace
-    if (p.ws_bytes > bytes) return FLD_ERR_TOO_LARGE;
+    if (p.ws_core > bytes) return FLD_ERR_TOO_LARGE;
     p.noalloc = true;
     p.own_pinned = false;
     p.hIO = p.io_host.data();
@@ -1586,7 +1732,7 @@ int32_t fld_plan_workspace_bytes(fld_plan_t plan, size_t* bytes) {
 
 int32_t fld_plan_bind_workspace(fld_plan_t plan, void* dev, size_t bytes) {
     if (!plan || !dev) return FLD_ERR_INVALID_ARG;
-    if (bytes < plan->p.ws_bytes) return FLD_ERR_NO_WORKSPACE;
+    if (bytes < plan->p.ws_core) return FLD_ERR_NO_WORKSPACE;
     try {
         fld::DeviceGuard dg(plan->p.device);
         if (!dg.ok) return FLD_ERR_HIP;
