@@ -24,12 +24,18 @@ constexpr int kSX = 128;
 constexpr int kCoarseThreads = 1024;
 constexpr int kCoarseCPT = 4;
 constexpr int kCoarseMaxLDS = kCoarseThreads * kCoarseCPT;   // 4096 cells
-// LDS tail: one 512-thread workgroup per grid (measured ahead of 256 and 1024); its
-// coarsest CG holds up to 4 cells a thread.
+// LDS tail: one 512-thread workgroup per grid (measured ahead of 256 and 1024), its first
+// and its coarsest level of at most 4 cells a thread (8, a 64^2 level: 48 us a call for 1024^2,
+// against 17 us and two launches of 5.5 us without that level).
 constexpr int kTailThreads = 512;
-constexpr int kTailCPT = 4;
-constexpr int kTailMaxCoarsest = kTailThreads * kTailCPT;    // 2048 cells
-constexpr int kTailWaveCells = 256;                         // tail levels run by one wavefront
+constexpr int kTailCells = 4 * kTailThreads;                 // 2048 cells: 32^2, 12^3
+constexpr int kTailMaxCoarsest = 4 * kTailThreads;           // 2048 cells
+constexpr int kMaxTail = 8;                                  // levels of a tail: one a wavefront
+constexpr int kTailWaveHalf = 128;                          // colour cells of a level swept by one wavefront
+// cells of one colour, rounded up a row
+__host__ __device__ inline int32_t tail_half(const int32_t n[3]) { return (n[0] + 1) / 2 * n[1] * n[2]; }
+// elements before and after the tail's iterates: the reach of a neighbour offset, and a spare
+__host__ __device__ inline int32_t tail_pad(const int32_t n[3]) { return n[2] == 1 ? n[0] + 2 : n[0] * n[1] + 2; }
 constexpr int kMarchNP = 128;                               // row-marching 2D window: positions (two a lane)
 constexpr int kMarchFz = 32;                                // rows per row-marching window
 constexpr int kMarchFzShort = 16;                           // rows where windows are few
@@ -384,9 +390,8 @@ void launch_tile(int dim, bool fp32, int bc, const LevelDesc* L, const GridState
                  int prolong, int restr, int c0, int from_xs, hipStream_t s);
 // bc: the plan has Dirichlet or periodic faces.
 void launch_tail(int dim, bool fp32, int bc, const LevelDesc* L, const GridState* S, JobList jl, size_t smem,
-                 int nu1, int nu2, int plain64, hipStream_t s);
-// LDS bytes of a tail whose finest level has cells n0 and whose levels halve down to
-// `levels` levels: x, b and DIM face arrays per level plus one coarsest vector.
+                 int cpc, int nu1, int nu2, int plain64, hipStream_t s);
+// cpc: cells of one colour of the first level a thread holds (1 or 2).
 constexpr size_t kTailLdsBudget = 150 * 1024;
 // select: 0 = active grids, 1 = inactive grids whose status is FLD_OK (convergence check).
 // zero_x: also clear the level-0 V-cycle iterate (FP64 or FP32 by `mixed`); mixed also

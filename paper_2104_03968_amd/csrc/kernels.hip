@@ -75,10 +75,41 @@ __device__ __forceinline__ int mirror(int i, int n) {
     return i < 0 ? -1 - i : (i >= n ? 2 * n - 1 - i : i);
 }
 
+template <int OFF>
+__device__ __forceinline__ double butterfly_add(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+    if constexpr (OFF >= 16) {
+        // the swap returns both halves' values: their sum is the same on either side
+        uint32_t l0, l1, h0, h1;
+        if constexpr (OFF == 32) {
+            const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
+        } else {
+            const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
+        }
+        return __builtin_bit_cast(double, ((uint64_t)h0 << 32) | l0) + __builtin_bit_cast(double, ((uint64_t)h1 << 32) | l1);
+    } else {
+        constexpr int ctrl = OFF == 8 ? 0x128 : (OFF == 4 ? 0x124 : (OFF == 2 ? 0x4E : 0xB1));
+        const uint32_t l = __builtin_amdgcn_update_dpp(0u, lo, ctrl, 0xF, 0xF, true);
+        const uint32_t h = __builtin_amdgcn_update_dpp(0u, hi, ctrl, 0xF, 0xF, true);
+        return v + __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
+    }
+}
+// Sum over the wavefront, on every lane (which must all be active): the xor butterfly from 32
+// down to 1, by register moves (a shuffle's LDS round trip takes ten times as long).  The
+// half-wave swaps give both halves' values; the rotations within rows of 16 reach the
+// lane l xor 8 (4) because the values already agree on lanes 16 (8) apart.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v = butterfly_add<32>(v);
+    v = butterfly_add<16>(v);
+    v = butterfly_add<8>(v);
+    v = butterfly_add<4>(v);
+    v = butterfly_add<2>(v);
+    return butterfly_add<1>(v);
 }
 
 // Barrier of the NT threads that run a phase: the workgroup, or for NT = 64 the one
@@ -2598,17 +2629,25 @@ k_tile(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
 }
 
 // ---------------------------------------------------------------------------
-// Tail: one workgroup per grid runs the whole V-cycle below a level T out of
-// LDS -- every tail level's x, b and face weights, plus the coarsest CG's
-// search direction -- so the coarse levels cost one launch instead of a few
-// per level.  The restriction from level T-1 left b_T in global memory and the
-// prolongation to level T-1 reads the correction x_T back from global memory.
+// Tail: one workgroup per grid runs the whole V-cycle below a level T (of at most
+// kTailCells cells), so the coarse levels cost one launch instead of a few per level.  The
+// restriction from level T-1 left b_T in global memory and the prolongation to level T-1
+// reads the correction x_T back from global memory.
+//
+// What bounds it is one workgroup's chain of phases (12 half sweeps a level), so a phase is
+// kept short: each thread owns the same cells of a level for all its sweeps and keeps their
+// faces, diagonal and its reciprocal in registers over the whole kernel; only the iterates are
+// read from LDS, at constant offsets (a neighbour past the level's edge is some other finite
+// value there, of weight zero).  The workgroup sweeps the first level, and the second where
+// it has more than a wavefront's cells; every level below belongs to a wavefront of its own
+// (no workgroup barriers within a level, and all levels' operators are set up at once).
+// 1024^2 in FP64: 30 -> 15 us a call; 256^3: 23 -> 15 us; a 45 x 25 coarsest level: 41 -> 18 us.
 // ---------------------------------------------------------------------------
-// Geometry of one tail level and the LDS offsets (in elements from the start of
-// the tail's dynamic LDS) of its arrays.  The arrays are addressed as that base
-// plus an offset in the kernel itself, so the compiler sees LDS pointers and
-// emits ds_* instructions (pointers read back from memory would be generic and
-// need flat instructions, which also wait on the vector memory counter).
+// Geometry of one tail level and the LDS offsets (in elements from the start of the tail's
+// dynamic LDS) of its arrays.  The arrays are addressed as that base plus an offset in the
+// kernel itself, so the compiler sees LDS pointers and emits ds_* instructions (pointers
+// read back from memory would be generic and need flat instructions, which also wait on
+// the vector memory counter).
 struct TailGeom {
     int32_t n[3];
     int32_t ncell;
@@ -2616,287 +2655,453 @@ struct TailGeom {
     float rhx;           // 1 / hx
     float rny;           // 1 / ny
     float rnx;           // 1 / nx
-    int32_t ox, ob, ow[3];
-    int32_t oa, has_a;   // Dirichlet ghost couplings (plans with Dirichlet faces)
+    int32_t ox, ob;      // (the first level has no b here)
     int32_t pm;          // neighbour mask (nb_mask): periodic axes, continuous faces
 };
 
-template <typename T>
-struct TailLevel {
-    int32_t n[3];
-    int32_t ncell;
-    int32_t hx;
-    float rhx;
-    float rny;
-    float rnx;
-    T* x;
-    T* b;
-    T* w[3];
-    T* a;
-    int32_t has_a;
-    int32_t pm;
-};
-
-template <typename T>
-__device__ __forceinline__ TailLevel<T> tl_at(const TailGeom& g, T* base) {
-    TailLevel<T> t;
-    t.n[0] = g.n[0]; t.n[1] = g.n[1]; t.n[2] = g.n[2];
-    t.ncell = g.ncell;
-    t.hx = g.hx;
-    t.rhx = g.rhx;
-    t.rny = g.rny;
-    t.rnx = g.rnx;
-    t.x = base + g.ox;
-    t.b = base + g.ob;
-    for (int a = 0; a < 3; ++a) t.w[a] = base + g.ow[a];
-    t.a = base + g.oa;
-    t.has_a = g.has_a;
-    t.pm = g.pm;
-    return t;
-}
-constexpr int kMaxTail = 16;
 
 // q / d for 0 <= q < 2^20 and d <= 2^10 through a float reciprocal: (q + 1/2)/d
 // lies at least 1/(2d) from an integer, far beyond the float rounding error.
 __device__ __forceinline__ int fdiv(int q, float rd) { return (int)(((float)q + 0.5f) * rd); }
 
-template <int DIM, typename T>
-__device__ __forceinline__ void tl_coords(const TailLevel<T>& lv, int c, int& i, int& j, int& k) {
-    const int r = fdiv(c, lv.rnx);
-    i = c - r * lv.n[0];
+// Cell u of this thread among the cells of `color`: its coordinates, and whether there is one.
+template <int DIM>
+__device__ __forceinline__ bool tail_cell(const TailGeom& g, int color, int m, int& i, int& j, int& k) {
+    const int r = fdiv(m, g.rhx);
+    j = r;
+    k = 0;
     if (DIM == 3) {
-        k = fdiv(r, lv.rny);
-        j = r - k * lv.n[1];
-    } else {
-        j = r;
-        k = 0;
+        k = fdiv(r, g.rny);
+        j = r - k * g.n[1];
     }
+    i = 2 * (m - r * g.hx) + ((j + k + color) & 1);
+    return m < g.hx * g.n[1] * g.n[2] && i < g.n[0];
 }
 
-// Levels are passed by value: a copy in registers, since the LDS stores of a phase
-// could otherwise alias the descriptor table in LDS and force its re-reading.
-template <int DIM, typename T, bool BC, int NT>
-__device__ __forceinline__ void tl_half_sweep(const TailLevel<T> lv, int color) {
-    const int pmask = BC ? lv.pm : 0;
-    const int sy = lv.n[0], sz = lv.n[0] * lv.n[1];
-    const int rows = lv.n[1] * lv.n[2];
-    for (int m = threadIdx.x; m < rows * lv.hx; m += NT) {
-        const int r = fdiv(m, lv.rhx);
-        int j = r, k = 0;
-        if (DIM == 3) {
-            k = fdiv(r, lv.rny);
-            j = r - k * lv.n[1];
-        }
-        const int i = 2 * (m - r * lv.hx) + ((j + k + color) & 1);
-        if (i >= lv.n[0]) continue;
-        const long c = i + j * sy + k * sz;
-        T s = lv.b[c], dg = T(1);
-        T wl, xl, wr, xr, wd, xd, wu, xu;
-        nb_lo(lv.w[0], lv.x, c, i, lv.n[0], 1, pmask, 0, wl, xl);
-        nb_hi(lv.w[0], lv.x, c, i, lv.n[0], 1, pmask, 0, wr, xr);
-        nb_lo(lv.w[1], lv.x, c, j, lv.n[1], sy, pmask, 1, wd, xd);
-        nb_hi(lv.w[1], lv.x, c, j, lv.n[1], sy, pmask, 1, wu, xu);
-        s += wl * xl; dg += wl;
-        s += wr * xr; dg += wr;
-        s += wd * xd; dg += wd;
-        s += wu * xu; dg += wu;
-        if (DIM == 3) {
-            T wb, xb, wf, xf;
-            nb_lo(lv.w[2], lv.x, c, k, lv.n[2], sz, pmask, 2, wb, xb);
-            nb_hi(lv.w[2], lv.x, c, k, lv.n[2], sz, pmask, 2, wf, xf);
-            s += wb * xb; dg += wb;
-            s += wf * xf; dg += wf;
-        }
-        if (BC && lv.has_a) dg += lv.a[c];
-        lv.x[c] = s / dg;
-    }
-    group_sync<NT>();
-}
+// A thread's cells of one level, CPC of each colour: place in the level's iterate, operator
+// and right-hand side.  A missing cell sits on the spare element with all weights zero.
+// BC: neighbours wrap on periodic axes, a continuous face is cut out of its cell's row, and
+// Dirichlet couplings add to the diagonal (nb_lo, nb_hi).
+template <int DIM, typename T, bool BC, int CPC>
+struct TailCells {
+    T b[2][CPC], w[2][CPC][2 * DIM], dg[2][CPC], rd[2][CPC], ad[2][BC ? CPC : 1];
+    int at[2][CPC];
+    uint32_t nb[2][BC ? CPC : 1][DIM];                         // neighbours below and above an axis (16 bits each)
 
-// The V-cycle of the tail levels from m0 down (level m0's b set, its x zero or warm),
-// run by NT threads: the workgroup, or one wavefront for small levels.
-template <int DIM, typename T, bool BC, int NT, int CPT>
-__device__ __forceinline__ void tail_vcycle(const TailGeom* tl, T* sbase, int m0, int nl, int nu1, int nu2, T* p_sh,
-                                            double* red) {
-    // descend
-    for (int m = m0; m + 1 < nl; ++m) {
-        const TailLevel<T> f = tl_at(tl[m], sbase);
-        const TailLevel<T> cT = tl_at(tl[m + 1], sbase);
-        for (int it = 0; it < nu1; ++it) {
-            tl_half_sweep<DIM, T, BC, NT>(f, 0);
-            tl_half_sweep<DIM, T, BC, NT>(f, 1);
+    // tid: this thread among the NT that share the level; spare: an element of x that no cell
+    // has; with_b: the right-hand side too (else set_b later)
+    template <int NT>
+    __device__ __forceinline__ void load(const TailGeom& g, const LevelDesc& d, bool has_a, int spare, int tid,
+                                         bool with_b) {
+        const gptr<T> w0 = as_global(Arr<T>::w(d, 0)), w1 = as_global(Arr<T>::w(d, 1));
+        const gptr<T> w2 = as_global(DIM == 3 ? Arr<T>::w(d, 2) : Arr<T>::w(d, 0));
+        const gptr<T> bs = as_global(with_b ? Arr<T>::b(d) : Arr<T>::w(d, 0));
+        const gptr<T> as = as_global(has_a ? Arr<T>::ad(d) : Arr<T>::w(d, 0));
+        const int sy = g.n[0], sz = g.n[0] * g.n[1];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int u = 0; u < CPC; ++u) {
+                int i, j, k;
+                const bool ok = tail_cell<DIM>(g, q, tid + u * NT, i, j, k);
+                const int c = ok ? i + j * sy + k * sz : 0;
+                at[q][u] = ok ? c : spare;
+                const int ijk[3] = {i, j, k}, st[3] = {1, sy, sz};
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) {
+                    const gptr<T> wa = a == 0 ? w0 : (a == 1 ? w1 : w2);
+                    const int n = g.n[a], v = ijk[a], s = st[a];
+                    const bool per = BC && ((g.pm >> a) & 1);
+                    const bool cut_lo = BC && v == n - 1 && ((g.pm >> (4 + 2 * a)) & 1);
+                    const bool cut_hi = BC && v == 0 && ((g.pm >> (3 + 2 * a)) & 1);
+                    const int lo = v > 0 ? c - s : (per ? c + (n - 1) * s : c);
+                    const int hi = v + 1 < n ? c + s : (per ? c - (n - 1) * s : c);
+                    const T wl = wa[c], wh = wa[ok ? hi : 0];
+                    w[q][u][2 * a] = ok && (v > 0 || per) && !cut_lo ? wl : T(0);
+                    w[q][u][2 * a + 1] = ok && (v + 1 < n || per) && !cut_hi ? wh : T(0);
+                    if constexpr (BC) nb[q][u][a] = ok ? lo | (hi << 16) : spare | (spare << 16);
+                }
+                const T bv = bs[c];
+                b[q][u] = ok ? bv : T(0);
+                if constexpr (BC) {
+                    const T av = as[c];
+                    ad[q][u] = ok && has_a ? av : T(0);
+                }
+            }
         }
-        for (int c = threadIdx.x; c < cT.ncell; c += NT) {
-            int I, J, K;
-            tl_coords<DIM, T>(cT, c, I, J, K);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int u = 0; u < CPC; ++u) {
+                T d = T(1);
+#pragma unroll
+                for (int f = 0; f < 2 * DIM; ++f) d += w[q][u][f];
+                if (BC && has_a) d += ad[q][u];
+                dg[q][u] = d;
+                rd[q][u] = T(1) / d;
+            }
+        }
+    }
+    __device__ __forceinline__ void set_b(const TailGeom& g, const T* bs) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int u = 0; u < CPC; ++u) {
+                const bool ok = at[q][u] < g.ncell;
+                const T v = bs[ok ? at[q][u] : 0];
+                b[q][u] = ok ? v : T(0);
+            }
+    }
+    // the value of x across face f of cell (q, u)
+    __device__ __forceinline__ T nbr(const T* x, const TailGeom& g, int q, int u, int f) const {
+        if constexpr (BC) return x[f & 1 ? nb[q][u][f >> 1] >> 16 : nb[q][u][f >> 1] & 0xffff];
+        const int st = f < 2 ? 1 : (f < 4 ? g.n[0] : g.n[0] * g.n[1]);
+        return x[at[q][u] + (f & 1 ? st : -st)];
+    }
+    template <int NT>
+    __device__ __forceinline__ void half(T* x, const TailGeom& g, int q) const {
+        T v[CPC];
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            T s = b[q][u];
+#pragma unroll
+            for (int f = 0; f < 2 * DIM; ++f) s += w[q][u][f] * nbr(x, g, q, u, f);
+            v[u] = div_by(s, dg[q][u], rd[q][u]);
+        }
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) x[at[q][u]] = v[u];
+        group_sync<NT>();
+    }
+    __device__ __forceinline__ T residual(const T* x, const TailGeom& g, int q, int u, bool has_a) const {
+        const T xc = x[at[q][u]];
+        T r = b[q][u] - xc;
+#pragma unroll
+        for (int f = 0; f < 2 * DIM; ++f) r -= w[q][u][f] * (xc - nbr(x, g, q, u, f));
+        if (BC && has_a) r -= ad[q][u] * xc;
+        return r;
+    }
+    // nu sweeps, then the residual averaged onto the coarse level's right-hand side
+    template <int NT>
+    __device__ __forceinline__ void down(T* x, T* res, const TailGeom& g, const TailGeom& cg, T* cx, T* cb, int nu,
+                                         bool has_a, int tid) const {
+        for (int it = 0; it < nu; ++it) {
+            half<NT>(x, g, 0);
+            half<NT>(x, g, 1);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int u = 0; u < CPC; ++u)
+                res[at[q][u] < g.ncell ? at[q][u] : g.ncell] = residual(x, g, q, u, has_a);
+        group_sync<NT>();
+        const int sy = g.n[0], sz = g.n[0] * g.n[1];
+        for (int c = tid; c < cg.ncell; c += NT) {
+            const int r = fdiv(c, cg.rnx), I = c - r * cg.n[0];
+            int J = r, K = 0;
+            if (DIM == 3) {
+                K = fdiv(r, cg.rny);
+                J = r - K * cg.n[1];
+            }
+            const T* f0 = res + 2 * I + 2 * J * sy + (DIM == 3 ? 2 * K * sz : 0);
             T sum = T(0);
 #pragma unroll
-            for (int q = 0; q < (1 << DIM); ++q)
-                sum += residual_at<DIM, T>(f.x, f.b, f.w[0], f.w[1], f.w[2], f.n, 2 * I + (q & 1),
-                                           2 * J + ((q >> 1) & 1), DIM == 3 ? 2 * K + (q >> 2) : 0, f.a,
-                                           BC && f.has_a != 0, BC ? f.pm : 0);
-            cT.b[c] = sum * T(DIM == 3 ? 0.125 : 0.25);
-            cT.x[c] = T(0);
+            for (int q = 0; q < (1 << DIM); ++q) sum += f0[(q & 1) + ((q >> 1) & 1) * sy + (DIM == 3 ? (q >> 2) * sz : 0)];
+            cb[c] = sum * T(DIM == 3 ? 0.125 : 0.25);
+            cx[c] = T(0);
         }
         group_sync<NT>();
     }
-    // coarsest: CG from the current x (zero unless the grid has a single level)
-    {
-        const TailLevel<T> cT = tl_at(tl[nl - 1], sbase);
-        block_cg<DIM, T, NT, CPT>(cT.n, cT.w[0], cT.w[1], cT.w[2], cT.b, cT.x, true, p_sh, red, cT.a,
-                                  BC && cT.has_a != 0, BC ? cT.pm : 0);
-    }
-    // ascend
-    for (int m = nl - 2; m >= m0; --m) {
-        const TailLevel<T> f = tl_at(tl[m], sbase);
-        const TailLevel<T> cT = tl_at(tl[m + 1], sbase);
-        for (int c = threadIdx.x; c < f.ncell; c += NT) {
-            int i, j, k;
-            tl_coords<DIM, T>(f, c, i, j, k);
-            f.x[c] += cT.x[(i >> 1) + cT.n[0] * ((j >> 1) + cT.n[1] * (k >> 1))];
-        }
+    // add the coarse correction, then nu sweeps
+    template <int NT>
+    __device__ __forceinline__ void up(T* x, const TailGeom& g, const TailGeom& cg, const T* cx, int nu,
+                                       int tid) const {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int u = 0; u < CPC; ++u) {
+                int i, j, k;
+                const bool ok = tail_cell<DIM>(g, q, tid + u * NT, i, j, k);
+                const T v = cx[ok ? (i >> 1) + cg.n[0] * ((j >> 1) + cg.n[1] * (k >> 1)) : 0];
+                if (ok) x[at[q][u]] += v;
+            }
         group_sync<NT>();
-        for (int it = 0; it < nu2; ++it) {
-            tl_half_sweep<DIM, T, BC, NT>(f, 1);
-            tl_half_sweep<DIM, T, BC, NT>(f, 0);
+        for (int it = 0; it < nu; ++it) {
+            half<NT>(x, g, 1);
+            half<NT>(x, g, 0);
         }
+    }
+};
+
+// The sum of three values over the NT threads, on every thread, in a fixed order.
+template <int NT>
+__device__ __forceinline__ void group_sum3(double v[3], double* sh) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] = wave_sum(v[i]);
+    if constexpr (NT > 64) {
+        constexpr int NW = NT / 64;
+        const int wid = threadIdx.x >> 6;
+        __syncthreads();                                       // sh may still be read from a previous call
+        if ((threadIdx.x & 63) == 0)
+            for (int i = 0; i < 3; ++i) sh[3 * wid + i] = v[i];
+        __syncthreads();
+        v[0] = v[1] = v[2] = 0.0;
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+            for (int i = 0; i < 3; ++i) v[i] += sh[3 * k + i];
     }
 }
 
-// BC: the plan has Dirichlet or periodic faces (extra diagonal, wrapped neighbours).
+// Coarsest level: conjugate gradients on the black cells with the red ones eliminated (the
+// Schur complement of the red-black splitting, whose condition is that of the level's
+// operator over four: half the iterations of CG on all cells), preconditioned by the diagonal,
+// from the stored x to a 1e-6 residual relative to its start (the red cells' residual is
+// zero, so the black cells' is the level's).  One reduction an iteration (Chronopoulos and
+// Gear's recurrences).  The level must split red-black: no periodic axis of an odd length.
+template <int DIM, typename T, bool BC, int NT, int CPC>
+__device__ __forceinline__ void tail_cg(const TailCells<DIM, T, BC, CPC>& c, const TailGeom& g, bool has_a, T* x, T* y,
+                                        double* sh) {
+    double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            const T r = c.residual(x, g, q, u, has_a);
+            v[0] += (double)r * (double)r;
+        }
+    group_sum3<NT>(v, sh);
+    const double tol2 = 1e-12 * v[0];                          // (1e-6)^2 relative
+    if (!(v[0] > 0.0)) return;                                 // uniform
+    c.template half<NT>(x, g, 0);                              // the red cells' residual becomes zero
+    T xb[CPC], r[CPC], p[CPC], s[CPC];
+#pragma unroll
+    for (int u = 0; u < CPC; ++u) {
+        xb[u] = x[c.at[1][u]];
+        r[u] = c.residual(x, g, 1, u, has_a);
+        p[u] = s[u] = T(0);
+    }
+    const int maxit = g.ncell < 2000 ? g.ncell + 4 : 2000;
+    double gam = 0.0, alpha = 0.0;
+    for (int it = 0; it < maxit; ++it) {
+        // z = r / diagonal, t = (faces z) / diagonal on the red cells, w = S z
+        T z[CPC], w[CPC];
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            z[u] = r[u] * c.rd[1][u];
+            y[c.at[1][u]] = z[u];
+        }
+        group_sync<NT>();
+        T tr[CPC];
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            T t = T(0);
+#pragma unroll
+            for (int f = 0; f < 2 * DIM; ++f) t += c.w[0][u][f] * c.nbr(y, g, 0, u, f);
+            tr[u] = t * c.rd[0][u];
+        }
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) y[c.at[0][u]] = tr[u];
+        group_sync<NT>();
+        v[0] = v[1] = v[2] = 0.0;
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            T t = c.dg[1][u] * z[u];
+#pragma unroll
+            for (int f = 0; f < 2 * DIM; ++f) t -= c.w[1][u][f] * c.nbr(y, g, 1, u, f);
+            w[u] = t;
+            v[0] += (double)r[u] * (double)z[u];
+            v[1] += (double)t * (double)z[u];
+            v[2] += (double)r[u] * (double)r[u];
+        }
+        group_sum3<NT>(v, sh);
+        if (!(v[2] > tol2)) break;
+        const double beta = it ? v[0] / gam : 0.0;
+        const double den = v[1] - (it ? beta * v[0] / alpha : 0.0);
+        if (!(den > 0.0)) break;
+        alpha = v[0] / den;
+        gam = v[0];
+        const T al = (T)alpha, be = (T)beta;
+#pragma unroll
+        for (int u = 0; u < CPC; ++u) {
+            p[u] = z[u] + be * p[u];
+            s[u] = w[u] + be * s[u];
+            xb[u] += al * p[u];
+            r[u] -= al * s[u];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CPC; ++u) x[c.at[1][u]] = xb[u];
+    group_sync<NT>();
+    c.template half<NT>(x, g, 0);
+}
+
+// The coarsest level's solve by the whole workgroup, from x.
 template <int DIM, typename T, bool BC>
+__device__ __forceinline__ void tail_coarsest(const TailGeom& g, const LevelDesc& d, const T* bs, bool has_a, bool split,
+                                              T* x, T* y, int spare, double* sh) {
+    constexpr int NT = kTailThreads, CPC = kTailMaxCoarsest / 2 / NT;
+    if constexpr (BC) {
+        if (!split && g.ncell <= 64) {                         // a wavefront needs no barriers
+            if (threadIdx.x < 64)
+                block_cg<DIM, T, 64, 1>(g.n, Arr<T>::w(d, 0), Arr<T>::w(d, 1), DIM == 3 ? Arr<T>::w(d, 2) : nullptr, bs,
+                                        x, true, y, sh, Arr<T>::ad(d), has_a, g.pm);
+            return;
+        }
+        if (!split) {
+            block_cg<DIM, T, NT, 2 * CPC>(g.n, Arr<T>::w(d, 0), Arr<T>::w(d, 1), DIM == 3 ? Arr<T>::w(d, 2) : nullptr, bs,
+                                          x, true, y, sh, Arr<T>::ad(d), has_a, g.pm);
+            return;
+        }
+    }
+    TailCells<DIM, T, BC, CPC> c;
+    c.template load<NT>(g, d, has_a, spare, threadIdx.x, false);
+    c.set_b(g, bs);
+    tail_cg<DIM, T, BC, NT, CPC>(c, g, has_a, x, y, sh);
+}
+
+// The same as a call, for a coarsest level below others (their operators stay in the caller's
+// registers; inlined, its own would make them spill on every path): oy, spare and the level's
+// arrays as offsets in the tail's LDS.
+template <int DIM, typename T, bool BC>
+__device__ __attribute__((noinline)) void tail_coarsest_below(const TailGeom* gp, const LevelDesc* d, int oy, int spare,
+                                                              bool has_a, bool split, double* sh) {
+    extern __shared__ __align__(16) unsigned char tail_smem[];
+    T* const base = reinterpret_cast<T*>(tail_smem);
+    const TailGeom g = *gp;
+    tail_coarsest<DIM, T, BC>(g, *d, base + g.ob, has_a, split, base + g.ox, base + oy, spare - g.ox, sh);
+}
+
+// BC: the plan has Dirichlet or periodic faces (extra diagonal, wrapped neighbours).  CPC: the
+// cells of one colour of the first level a thread holds.
+template <int DIM, typename T, bool BC, int CPC>
 __global__ void __launch_bounds__(kTailThreads)
 k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int nu1, int nu2,
        int plain64) {
     extern __shared__ __align__(16) unsigned char tail_smem[];
     __shared__ TailGeom tl[kMaxTail];
-    __shared__ int32_t off[kMaxTail + 1];
-    __shared__ double red[2 * kTailThreads / 64];
+    __shared__ int32_t cells[kMaxTail];
+    __shared__ double sh[3 * kTailThreads / 64];
+    constexpr int NT = kTailThreads, CPW = kTailWaveHalf / 64;
     const int first = job_level(jl, blockIdx.x);
     const LevelDesc& d0 = L[first];
-    if (!S[d0.sidx].active) return;
-    const int hasa = (BC && Arr<T>::ad(d0) != nullptr) ? 1 : 0;
+    const int act = S[d0.sidx].active;
+    const bool has_a = BC && Arr<T>::ad(d0) != nullptr;
     // the grid's levels from `first` down are consecutive descriptors: thread m reads
     // level m's (no chain through the coarse links), then the LDS layout follows
     const int nl = min(d0.nlev - d0.level, kMaxTail);
-    const int m_own = threadIdx.x;
+    const int mo = threadIdx.x;
     int32_t nown[3] = {0, 0, 0};
-    if (m_own < nl) {
-        const LevelDesc& d = L[first + m_own];
+    int pm_own = 0;
+    if (mo < nl) {
+        const LevelDesc& d = L[first + mo];
         nown[0] = d.n[0]; nown[1] = d.n[1]; nown[2] = d.n[2];
-        off[m_own + 1] = (2 + DIM + hasa) * d.n[0] * d.n[1] * d.n[2];
+        pm_own = BC ? nb_mask(d) : 0;                           // continuous faces cut level 0 only
+        cells[mo] = nown[0] * nown[1] * nown[2];
     }
-    if (threadIdx.x == 0) off[0] = 0;
+    if (!act) return;                                          // uniform
     __syncthreads();
-    if (m_own < nl) {
-        int o = 0;
-        for (int j = 0; j < m_own; ++j) o += off[j + 1];
-        TailGeom& t = tl[m_own];
+    // LDS: a pad, every level's iterate, a pad; the first level's residuals (also the coarsest
+    // solve's vector) and a pad; every level's b
+    const int pad = tail_pad(d0.n);
+    int total = 2 * pad;
+    for (int j = 0; j < nl; ++j) total += cells[j];
+    if (mo < nl) {
+        TailGeom t;
         t.n[0] = nown[0]; t.n[1] = nown[1]; t.n[2] = nown[2];
-        t.ncell = nown[0] * nown[1] * nown[2];
+        t.ncell = cells[mo];
         t.hx = (nown[0] + 1) / 2;
         t.rhx = 1.0f / (float)t.hx;
         t.rnx = 1.0f / (float)nown[0];
         t.rny = 1.0f / (float)nown[1];
-        t.ox = o; o += t.ncell;
-        t.ob = o; o += t.ncell;
-        for (int a = 0; a < 3; ++a) {
-            t.ow[a] = o;                                   // unused past DIM
-            if (a < DIM) o += t.ncell;
+        t.pm = pm_own;
+        t.ox = pad;
+        t.ob = total + cells[0] + pad;
+        for (int j = 0; j < mo; ++j) {
+            t.ox += cells[j];
+            t.ob += cells[j];
         }
-        t.oa = o;                                          // unused without Dirichlet faces
-        t.has_a = hasa;
-        t.pm = BC ? nb_mask(L[first + m_own]) : 0;          // continuous faces cut level 0 only
+        tl[mo] = t;
     }
+    T* const base = reinterpret_cast<T*>(tail_smem);
+    // (finite: what a weight of zero is multiplied with)
+    for (int c = threadIdx.x; c < total + cells[0] + pad; c += NT) base[c] = T(0);
+    T* const res = base + total;
+    T* const y = res;
+    const int spare = total - 1;                               // of the upper pad: no cell's neighbour
+    const gptr<T> gx = as_global(Arr<T>::x(d0));
     __syncthreads();
-    T* const sbase = reinterpret_cast<T*>(tail_smem);
-    T* p_sh = sbase + (tl[nl - 1].oa + hasa * tl[nl - 1].ncell);   // the coarsest CG's search direction
-    // load every tail level's weights, and b and (warm) x of the first; loads of a
-    // level are issued together, then stored
-    for (int m = 0; m < nl; ++m) {
-        const LevelDesc& d = L[first + m];
-        const TailLevel<T> t = tl_at(tl[m], sbase);
-        const gptr<T> s0 = as_global(Arr<T>::w(d, 0));
-        const gptr<T> s1 = as_global(Arr<T>::w(d, 1));
-        const gptr<T> s2 = as_global((DIM == 3) ? Arr<T>::w(d, 2) : Arr<T>::w(d, 0));
-        const bool lead = (m == 0);
-        const bool warm = lead && plain64 && d.level == 0;
-        const gptr<T> bsrc = as_global(Arr<T>::b(d));
-        const gptr<T> xsrc = as_global(Arr<T>::x(d));
-        const gptr<T> asrc = as_global(hasa ? Arr<T>::ad(d) : Arr<T>::w(d, 0));
-        for (int c = threadIdx.x; c < t.ncell; c += kTailThreads) {
-            const T a0 = s0[c], a1 = s1[c];
-            const T a2 = (DIM == 3) ? s2[c] : T(0);
-            if (hasa) t.a[c] = asrc[c];
-            const T bb = lead ? bsrc[c] : T(0);
-            const T xx = warm ? xsrc[c] : T(0);
-            t.w[0][c] = a0;
-            t.w[1][c] = a1;
-            if (DIM == 3) t.w[2][c] = a2;
-            if (lead) {
-                t.b[c] = bb;
-                t.x[c] = xx;
-            }
-        }
+    const TailGeom g0 = tl[0], gl = tl[nl - 1];
+    const bool warm = plain64 && d0.level == 0;
+    T* const x0 = base + g0.ox;
+    // whether the coarsest level splits red-black with a symmetric operator
+    bool split = true;
+    if constexpr (BC) {
+        split = (gl.pm >> 3) == 0;
+        for (int a = 0; a < DIM; ++a) split = split && !(((gl.pm >> a) & 1) && (gl.n[a] & 1));
     }
-    __syncthreads();
-    // Levels of at most kTailWaveCells cells run on one wavefront, without workgroup
-    // barriers (they leave most of the block idle anyway): from the first such level
-    // ws down, when the coarsest level has at most 64 cells (the wavefront's CG then
-    // sums its products in the order the whole block would).
-    int ws = nl;
-    if (tl[nl - 1].ncell <= 64) {
-        ws = nl - 1;
-        while (ws > 0 && tl[ws - 1].ncell <= kTailWaveCells) --ws;
-    }
-    if (ws == nl) {
-        tail_vcycle<DIM, T, BC, kTailThreads, kTailCPT>(tl, sbase, 0, nl, nu1, nu2, p_sh, red);
-    } else {
-        // the workgroup smooths and restricts the levels above ws, one wavefront runs
-        // the V-cycle from ws, the workgroup prolongs and smooths back up
-        for (int m = 0; m < ws; ++m) {
-            const TailLevel<T> f = tl_at(tl[m], sbase);
-            const TailLevel<T> cT = tl_at(tl[m + 1], sbase);
-            for (int it = 0; it < nu1; ++it) {
-                tl_half_sweep<DIM, T, BC, kTailThreads>(f, 0);
-                tl_half_sweep<DIM, T, BC, kTailThreads>(f, 1);
-            }
-            for (int c = threadIdx.x; c < cT.ncell; c += kTailThreads) {
-                int I, J, K;
-                tl_coords<DIM, T>(cT, c, I, J, K);
-                T sum = T(0);
-#pragma unroll
-                for (int q = 0; q < (1 << DIM); ++q)
-                    sum += residual_at<DIM, T>(f.x, f.b, f.w[0], f.w[1], f.w[2], f.n, 2 * I + (q & 1),
-                                               2 * J + ((q >> 1) & 1), DIM == 3 ? 2 * K + (q >> 2) : 0, f.a,
-                                               BC && f.has_a != 0, BC ? f.pm : 0);
-                cT.b[c] = sum * T(DIM == 3 ? 0.125 : 0.25);
-                cT.x[c] = T(0);
-            }
-            __syncthreads();
+    if (nl == 1) {
+        // the only level: at most kTailMaxCoarsest cells, solved from the stored x (warm) or zero
+        const gptr<T> gb = as_global(Arr<T>::b(d0));
+        for (int c = threadIdx.x; c < g0.ncell; c += NT) {
+            base[g0.ob + c] = gb[c];
+            if (warm) x0[c] = gx[c];
         }
-        if (threadIdx.x < 64) tail_vcycle<DIM, T, BC, 64, 1>(tl, sbase, ws, nl, nu1, nu2, p_sh, red);
         __syncthreads();
-        for (int m = ws - 1; m >= 0; --m) {
-            const TailLevel<T> f = tl_at(tl[m], sbase);
-            const TailLevel<T> cT = tl_at(tl[m + 1], sbase);
-            for (int c = threadIdx.x; c < f.ncell; c += kTailThreads) {
-                int i, j, k;
-                tl_coords<DIM, T>(f, c, i, j, k);
-                f.x[c] += cT.x[(i >> 1) + cT.n[0] * ((j >> 1) + cT.n[1] * (k >> 1))];
-            }
-            __syncthreads();
-            for (int it = 0; it < nu2; ++it) {
-                tl_half_sweep<DIM, T, BC, kTailThreads>(f, 1);
-                tl_half_sweep<DIM, T, BC, kTailThreads>(f, 0);
-            }
+        tail_coarsest<DIM, T, BC>(g0, d0, base + g0.ob, has_a, split, x0, y, spare - g0.ox, sh);
+        __syncthreads();
+        for (int c = threadIdx.x; c < g0.ncell; c += NT) gx[c] = x0[c];
+        return;
+    }
+    // every level's operator into its threads' registers: the first level's on all, the second's
+    // too where it is no wavefront's, wavefront m's level m
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const TailGeom g1 = tl[1];
+    // (a 3D level's coarser one has at most an eighth of its cells: never more than a wavefront's,
+    // unless it is the coarsest)
+    const bool wide1 = tail_half(g1.n) > kTailWaveHalf;
+    TailCells<DIM, T, BC, CPC> c0;
+    TailCells<DIM, T, BC, 1> c1;
+    TailCells<DIM, T, BC, CPW> cw;
+    c0.template load<NT>(g0, d0, has_a, spare - g0.ox, threadIdx.x, true);
+    if (DIM == 2 && wide1 && nl > 2) c1.template load<NT>(g1, L[first + 1], has_a, spare - g1.ox, threadIdx.x, false);
+    const int mw = wide1 ? 2 : 1;                              // first level of a wavefront's own
+    const bool mine = wave >= mw && wave < nl;
+    TailGeom gm = tl[mine ? wave : 0], gc = tl[mine && wave + 1 < nl ? wave + 1 : 0];
+    if (mine) cw.template load<64>(gm, L[first + wave], has_a, spare - gm.ox, lane, false);
+    if (warm)
+        for (int c = threadIdx.x; c < g0.ncell; c += NT) x0[c] = gx[c];
+    __syncthreads();
+    c0.template down<NT>(x0, res, g0, g1, base + g1.ox, base + g1.ob, nu1, has_a, threadIdx.x);
+    if (DIM == 2 && wide1 && nl > 2) {
+        const TailGeom g2 = tl[2];
+        c1.set_b(g1, base + g1.ob);
+        c1.template down<NT>(base + g1.ox, res, g1, g2, base + g2.ox, base + g2.ob, nu1, has_a, threadIdx.x);
+    }
+    for (int m = mw; m + 1 < nl; ++m) {
+        if (wave == m) {
+            cw.set_b(gm, base + gm.ob);
+            cw.template down<64>(base + gm.ox, res, gm, gc, base + gc.ox, base + gc.ob, nu1, has_a, lane);
         }
+        __syncthreads();
     }
-    {
-        const gptr<T> xdst = as_global(Arr<T>::x(L[first]));
-        const TailLevel<T> t0 = tl_at(tl[0], sbase);
-        for (int c = threadIdx.x; c < t0.ncell; c += kTailThreads) xdst[c] = t0.x[c];
+    if (split && nl > mw) {
+        if (wave == nl - 1) {
+            cw.set_b(gm, base + gm.ob);
+            tail_cg<DIM, T, BC, 64, CPW>(cw, gm, has_a, base + gm.ox, y, sh);
+        }
+    } else {
+        tail_coarsest_below<DIM, T, BC>(&tl[nl - 1], &L[first + nl - 1], total, spare, has_a, split, sh);
     }
+    __syncthreads();
+    for (int m = nl - 2; m >= mw; --m) {
+        if (wave == m) cw.template up<64>(base + gm.ox, gm, gc, base + gc.ox, nu2, lane);
+        __syncthreads();
+    }
+    if (DIM == 2 && wide1 && nl > 2) {
+        const TailGeom g2 = tl[2];
+        c1.template up<NT>(base + g1.ox, g1, g2, base + g2.ox, nu2, threadIdx.x);
+    }
+    c0.template up<NT>(x0, g0, g1, base + g1.ox, nu2, threadIdx.x);
+    for (int c = threadIdx.x; c < g0.ncell; c += NT) gx[c] = x0[c];
 }
 
 // ---------------------------------------------------------------------------
@@ -3949,7 +4154,11 @@ void launch_tile(int dim, bool fp32, int bc, const LevelDesc* L, const GridState
 
 template <int DIM, typename T, bool BC>
 static hipError_t tail_lds(size_t smem) {
-    return hipFuncSetAttribute((const void*)k_tail<DIM, T, BC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    for (const void* k : {(const void*)k_tail<DIM, T, BC, 1>, (const void*)k_tail<DIM, T, BC, 2>}) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 int prepare_tail(int dim, bool fp32, size_t smem) {
     hipError_t e0, e1;
@@ -3964,16 +4173,18 @@ int prepare_tail(int dim, bool fp32, size_t smem) {
 }
 
 void launch_tail(int dim, bool fp32, int bc, const LevelDesc* L, const GridState* S, JobList jl, size_t smem,
-                 int nu1, int nu2, int plain64, hipStream_t s) {
+                 int cpc, int nu1, int nu2, int plain64, hipStream_t s) {
     if (jl.njobs <= 0) return;
     // list: each grid's first tail level; its b and the face arrays of every tail level
     // (2^d / (2^d - 1) times the first level's) read once, its x written
     if (acct_add(jl.cells * (fp32 ? 4.0 : 8.0) * (2.0 + dim * (double)(1 << dim) / ((1 << dim) - 1)))) return;
-#define FLD_TAIL(T_, B) hipLaunchKernelGGL((k_tail<D, T_, B>), dim3(jl.njobs), dim3(kTailThreads), smem, s, L, S, jl, nu1, nu2, plain64)
+#define FLD_TAIL(T_, B, C) hipLaunchKernelGGL((k_tail<D, T_, B, C>), dim3(jl.njobs), dim3(kTailThreads), smem, s, L, S, jl, nu1, nu2, plain64)
+#define FLD_TAIL_CPC(T_, B) do { if (cpc <= 1) FLD_TAIL(T_, B, 1); else FLD_TAIL(T_, B, 2); } while (0)
     FLD_DISPATCH_DIM(dim, {
-        if (bc) { if (fp32) FLD_TAIL(float, true); else FLD_TAIL(double, true); }
-        else { if (fp32) FLD_TAIL(float, false); else FLD_TAIL(double, false); }
+        if (bc) { if (fp32) FLD_TAIL_CPC(float, true); else FLD_TAIL_CPC(double, true); }
+        else { if (fp32) FLD_TAIL_CPC(float, false); else FLD_TAIL_CPC(double, false); }
     });
+#undef FLD_TAIL_CPC
 #undef FLD_TAIL
 }
 

@@ -282,32 +282,37 @@ static void build_levels(Plan& p) {
     }
 }
 
-// First level of each grid's LDS tail: the finest level from which every coarser
-// level (x, b, d face arrays) plus the coarsest CG's search direction fits the
-// LDS budget, with a coarsest level small enough for the block CG.
+// LDS bytes of grid g's tail from level t: every level's iterate and right-hand side, the first
+// level's residuals, three pads.
 static size_t tail_bytes(const Plan& p, int g, int t) {
-    const int l0 = p.level0[g], L = p.nlev[g];
-    const int dim = p.grids[g].ndim;
-    const size_t word = p.mixed ? 4 : 8;
-    size_t cells = 0;
-    for (int l = t; l < L; ++l) {
-        const LevelDesc& d = p.levels[l0 + l];
-        cells += (size_t)(2 + dim + (p.has_dir ? 1 : 0)) * d.n[0] * d.n[1] * d.n[2];
-    }
-    const LevelDesc& c = p.levels[l0 + L - 1];
-    cells += (size_t)c.n[0] * c.n[1] * c.n[2];
-    return cells * word;
+    const LevelDesc* const d = &p.levels[p.level0[g]];
+    size_t cells = 3 * (size_t)tail_pad(d[t].n) + (size_t)d[t].n[0] * d[t].n[1] * d[t].n[2];
+    for (int l = t; l < p.nlev[g]; ++l) cells += 2 * (size_t)d[l].n[0] * d[l].n[1] * d[l].n[2];
+    return cells * (p.mixed ? 4 : 8);
 }
 
+// Whether grid g's levels from t down fit the tail: the first level's colours in the
+// workgroup's registers, the second's too or in a wavefront's, those below in a wavefront's
+// each; the coarsest (which may be the second) of at most kTailMaxCoarsest cells.
+static bool tail_fits(const Plan& p, int g, int t) {
+    const LevelDesc* const d = &p.levels[p.level0[g]];
+    const int L = p.nlev[g];
+    if (L - t > kMaxTail || tail_bytes(p, g, t) > kTailLdsBudget) return false;
+    for (int l = t; l < L; ++l) {
+        const int64_t row = (int64_t)(d[l].n[0] + 1) / 2 * d[l].n[1];
+        const int64_t half = row * d[l].n[2];
+        const bool whole = l == t || (l == t + 1 && l == L - 1);   // on the workgroup, two cells a thread
+        if (half > (whole ? kTailCells / 2 : (l == t + 1 && p.grids[g].ndim == 2 ? kTailThreads : kTailWaveHalf))) return false;
+    }
+    return true;
+}
+
+// First level of each grid's LDS tail: the finest from which its levels fit.
 static void choose_tails(Plan& p) {
     p.tail_lev.assign(p.ngrids(), -1);
     for (int g = 0; g < p.ngrids(); ++g) {
-        const int L = p.nlev[g];
-        const LevelDesc& c = p.levels[p.level0[g] + L - 1];
-        if ((int64_t)c.n[0] * c.n[1] * c.n[2] > kTailMaxCoarsest) continue;
-        for (int t = 0; t < L; ++t) {
-            if (tail_bytes(p, g, t) <= kTailLdsBudget) { p.tail_lev[g] = t; break; }
-        }
+        for (int t = 0; t < p.nlev[g] && p.tail_lev[g] < 0; ++t)
+            if (tail_fits(p, g, t)) p.tail_lev[g] = t;
     }
 }
 
@@ -338,6 +343,10 @@ static void build_lists(Plan& p) {
             if (p.tail_lev[g] >= 0) {
                 D.tail.levels.push_back(l0 + p.tail_lev[g]);
                 D.tail_smem = std::max(D.tail_smem, tail_bytes(p, g, p.tail_lev[g]));
+                // (a level of one colour's cells a row longer than the other's: rows of ceil(nx / 2))
+                const LevelDesc& f = p.levels[l0 + p.tail_lev[g]];
+                const int64_t half = (int64_t)((f.n[0] + 1) / 2) * f.n[1] * f.n[2];
+                D.tail_cpc = std::max(D.tail_cpc, (int)((half + kTailThreads - 1) / kTailThreads));
             } else {
                 D.coarsest.levels.push_back(l0 + p.nlev[g] - 1);
             }
@@ -782,7 +791,7 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
         launch_restrict(dim, f32, p.dL, p.dS, D.restrict_[d].dev, p.nblk, s);
     }
     // the tail's levels are below the finest unless the whole grid lives in it
-    launch_tail(dim, f32, p.nb_bc(), p.dL, p.dS, tail, D.tail_smem, p.nuc1, p.nuc2, plain64, s);
+    launch_tail(dim, f32, p.nb_bc(), p.dL, p.dS, tail, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, plain64, s);
     launch_coarse_solve(dim, f32, p.dL, p.dS, coarsest, s);
     for (int d = D.maxdepth - 1; d >= d0; --d) {
         const int nu1 = d == 0 ? p.opts.nu1 : p.nuc1, nu2 = d == 0 ? p.opts.nu2 : p.nuc2;
@@ -866,7 +875,7 @@ static void enqueue_fmg(Plan& p, DimLists& D, hipStream_t s) {
     const bool f32 = p.mixed;
     for (int d = 0; d < D.maxdepth; ++d) launch_restrict_rhs(D.dim, f32, p.dL, p.dS, D.restrict_[d].dev, p.nblk, s);
     const int plain64 = (!p.krylov && !p.mixed) ? 1 : 0;
-    launch_tail(D.dim, f32, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, p.nuc1, p.nuc2, plain64, s);
+    launch_tail(D.dim, f32, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, plain64, s);
     launch_coarse_solve(D.dim, f32, p.dL, p.dS, D.coarsest.dev, s);
     // by dimension: the 3D stages below the two finest still pay for their V-cycles
     const int fd = p.opts.fmg_depths >= 0 ? p.opts.fmg_depths : (D.dim == 3 ? 3 : 2);
@@ -1567,7 +1576,7 @@ static int profile_kernel(Plan& p, int kernel, int level, int reps, hipStream_t 
                         launch_sweep3(p.mixed, p.dL, p.dS, D.sw3[level].dev, 0, 0, 0, D.fz_s[level], p.nblk, s);
                     break;
                 case FLD_KERNEL_TAIL:
-                    launch_tail(D.dim, p.mixed, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, p.nuc1, p.nuc2, 0, s);
+                    launch_tail(D.dim, p.mixed, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, 0, s);
                     break;
                 default: break;
             }
