@@ -419,7 +419,8 @@ void launch_output(int dim, const LevelDesc* L, JobList jl, const StepIO* io, in
                    hipStream_t s);
 void launch_count(const GridState* S, int ngrids, Control* ctrl, hipStream_t s);
 // Radiation moments of every level-0 cell of the listed grids (io indexed by grid).
-void launch_moments(int dim, const LevelDesc* L, JobList jl, const MomentsIO* io, double c, int limiter,
+// bc: the plan has faces other than zero flux.
+void launch_moments(int dim, int bc, const LevelDesc* L, JobList jl, const MomentsIO* io, double c, int limiter,
                     int nblk, hipStream_t s);
 void launch_set_active(GridState* S, int ngrids, int value, hipStream_t s);
 void launch_exchange(const ExchangeIO* io, int ngrids, int64_t max_n, double c, double a_rad,

@@ -1368,7 +1368,7 @@ static int moments(Plan& p, const double* const* E, const double* const* kr, con
     MomentsIO* d = p.dMo + (size_t)slot * G;
     FLD_HIP(hipMemcpyAsync(d, h, G * sizeof(MomentsIO), hipMemcpyHostToDevice, s));
     for (auto& D : p.dl)
-        if (!D.l0_cell.empty()) launch_moments(D.dim, p.dL, D.l0_cell.dev, d, p.opts.c, p.opts.limiter, cell_blocks(p), s);
+        if (!D.l0_cell.empty()) launch_moments(D.dim, p.any_bc, p.dL, D.l0_cell.dev, d, p.opts.c, p.opts.limiter, cell_blocks(p), s);
     FLD_HIP(hipGetLastError());
     FLD_HIP(hipEventRecord(p.mo_done[slot], s));
     return FLD_OK;
