@@ -222,6 +222,7 @@ enum FinMode : int32_t {
     FIN_PQ = 5,          // CG: alpha = rho / p . q
     FIN_CG = 6,          // CG: recursive ||r||^2, stop test
     FIN_R_FMG = 7,       // true residual after the full-multigrid start: counts a cycle, (re)starts CG
+    FIN_START = 8,       // FIN_B and FIN_R_INIT from k_start's partials
 };
 
 // Which levels a launch covers.  Level j of the list is LevelDesc levels[j];
@@ -325,6 +326,11 @@ struct Control {
 void launch_coeff(int dim, bool mixed, int bc, const LevelDesc* L, GridState* S, JobList jl,
                   const StepIO* io, double c, int limiter, int fin, double rtol, int max_cycles, int nblk,
                   hipStream_t s);
+// Start of a step under CG, zero-flux faces and one opacity: coefficients, b, x, initial
+// residual and all three norms (fin: finished in the last block, else a k_finalize with
+// FIN_START).  zero_x: also clear the V-cycle's level-0 iterate.
+void launch_start(int dim, bool mixed, const LevelDesc* L, GridState* S, JobList jl, const StepIO* io, double c,
+                  int limiter, int zero_x, int fin, double rtol, int max_cycles, int nblk, hipStream_t s);
 void launch_finalize(const LevelDesc* L, GridState* S, JobList jl, int mode, double rtol,
                      int max_cycles, hipStream_t s);
 // galerkin: coarse weights of R A P (piecewise-constant P, child-mean R); 0: rediscretised.

@@ -219,7 +219,8 @@ int plan_init(Plan& p, const fld_grid* grids, int ngrids, const fld_opts& opts);
 // init: initial per-grid solver states (nullptr: fresh).  Synchronous.
 int plan_bind(Plan& p, void* dev, size_t bytes, const GridState* init);
 // Per-step phases, asynchronous on s (the StepIO table must be on the device).
-int plan_prologue(Plan& p, hipStream_t s);               // coefficients, norms, initial residual
+// (tensor: the step gives one opacity per direction)
+int plan_prologue(Plan& p, hipStream_t s, bool tensor = false);   // coefficients, norms, initial residual
 void plan_cycle(Plan& p, hipStream_t s);                 // one V-cycle (+ CG update) for active grids
 void plan_verify(Plan& p, hipStream_t s);                // true residual of grids CG reported converged
 void plan_output(Plan& p, hipStream_t s);                // X -> E_out

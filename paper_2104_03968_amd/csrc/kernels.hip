@@ -349,11 +349,20 @@ k_finalize(const LevelDesc* __restrict__ L, GridState* __restrict__ S, JobList j
     __shared__ double sh[2 * kBlock / 64];
     const LevelDesc& d = L[job_level(jl, blockIdx.x)];
     GridState& g = S[d.sidx];
-    const bool run = (mode == FIN_B) || (mode == FIN_R_VERIFY ? (g.status == FLD_OK && !g.active) : g.active);
+    const bool run = (mode == FIN_B || mode == FIN_START) || (mode == FIN_R_VERIFY ? (g.status == FLD_OK && !g.active) : g.active);
     if (!run) return;                                // uniform per block
     double s2, s1;
     // the tiles of the list's reducing kernel (level-0 cell tiles, or the z-march tiles)
-    sum_parts(d.part, job_tiles(jl, blockIdx.x), mode == FIN_B ? 2 : 1, s2, s1, sh);
+    sum_parts(d.part, job_tiles(jl, blockIdx.x), mode == FIN_B || mode == FIN_START ? 2 : 1, s2, s1, sh);
+    if (mode == FIN_START) {
+        double r2, unused;
+        sum_parts(d.P[0], job_tiles(jl, blockIdx.x), 1, r2, unused, sh);
+        if (threadIdx.x == 0) {
+            finalize_grid(g, s2, s1, FIN_B, rtol, max_cycles);
+            if (g.active) finalize_grid(g, r2, 0.0, FIN_R_INIT, rtol, max_cycles);
+        }
+        return;
+    }
     if (threadIdx.x == 0) finalize_grid(g, s2, s1, mode, rtol, max_cycles);
 }
 
@@ -462,13 +471,16 @@ __device__ __forceinline__ void grad4_per_at(const double* __restrict__ F, int i
 // 1/3, Minerbo's two branches (meeting with equal value and slope at R = 3/2), or
 // Levermore and Pomraning's (coth R - 1/R)/R, by its series below R = 0.1 where
 // the difference cancels (the series truncation there is below 1e-16).
+// EXACT = false: the caller knows that it is not the exact Levermore-Pomraning one, whose tanh
+// (inlined for each cell of a thread) takes registers from the other limiters too.
+template <bool EXACT = true>
 __device__ __forceinline__ double limiter_of(double R, int limiter) {
     if (limiter == FLD_LIMITER_DIFFUSION) return 1.0 / 3.0;
     if (limiter == FLD_LIMITER_MINERBO) {
         if (R <= 1.5) return 2.0 / (3.0 + sqrt(9.0 + 12.0 * R * R));
         return 1.0 / (1.0 + R + sqrt(1.0 + 2.0 * R));
     }
-    if (limiter == FLD_LIMITER_LP_EXACT) {
+    if (EXACT && limiter == FLD_LIMITER_LP_EXACT) {
         if (R < 0.1) {
             const double r2 = R * R;
             return 1.0 / 3.0 +
@@ -500,11 +512,121 @@ __device__ __forceinline__ double face_w(double DL, double DR, double dt, double
     return dt * (2.0 * DL * DR / (DL + DR)) * (hinv * hinv);
 }
 
-// First pass of the coefficients: D = c lambda(R) / (kappa rho) once per level-0 cell,
+// Level arrays live in global memory, but pointers read from a LevelDesc carry no
+// address space, so accesses through them compile to flat loads and stores, which
+// also count against the LDS wait counter: a kernel that keeps global loads in
+// flight while it works on LDS must access them through global pointers.
+template <typename T> using gptr = __attribute__((address_space(1))) T*;
+template <typename T> __device__ __forceinline__ gptr<T> as_global(T* p) { return (gptr<T>)p; }
+
+// The 4th-order gradient of a field with mirrored ghosts at a thread's kCPT0 cells of a
+// level-0 tile.  Every load is issued before the first use, from clamped cells.
+template <int DIM>
+struct Grad4Cells {
+    long at[kCPT0];              // flat index of each cell (clamped into the level)
+    bool ok[kCPT0];
+    // offsets of the neighbours -2, -1, +1, +2 (mirrored); the cells share their column of x
+    // (and in 3D of y)
+    int ox[4], oy[DIM == 3 ? 1 : kCPT0][4];
+    long oz[DIM == 3 ? kCPT0 + 4 : 1];   // 3D: a thread's cells are one column; planes k0 - 2 .. k0 + kCPT0 + 1
+
+    __device__ __forceinline__ Grad4Cells(const LevelDesc& d, int lt) {
+        const long sz = (long)d.n[0] * d.n[1];
+        int k0 = 0;
+#pragma unroll
+        for (int m = 0; m < kCPT0; ++m) {
+            int i, j, k;
+            at[m] = l0_cell<DIM>(d, lt, m, i, j, k, ok[m]);
+            if (m == 0) k0 = k;
+            const int t[4] = {-2, -1, 1, 2};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (m == 0) ox[q] = mirror(i + t[q], d.n[0]) - i;
+                if (m == 0 || DIM == 2) oy[DIM == 3 ? 0 : m][q] = (mirror(j + t[q], d.n[1]) - j) * d.n[0];
+            }
+        }
+        if constexpr (DIM == 3) {
+            // (the last planes of a column that runs past the level are not used)
+            const int n2 = d.n[2];
+#pragma unroll
+            for (int z = 0; z < kCPT0 + 4; ++z)
+                oz[z] = (min(max(mirror(k0 - 2 + z, n2), 0), n2 - 1) - k0) * sz;
+        }
+    }
+    // v: the field at the cells (3D: from the column); g: the gradient there
+    __device__ __forceinline__ void operator()(const double* F_, const double c12[3], double v[kCPT0],
+                                               double g[kCPT0][3]) const {
+        const gptr<const double> F = as_global(F_);
+        double x[kCPT0][4], y[kCPT0][4], z[DIM == 3 ? kCPT0 + 4 : 1];
+#pragma unroll
+        for (int m = 0; m < kCPT0; ++m) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                x[m][q] = F[at[m] + ox[q]];
+                y[m][q] = F[at[m] + oy[DIM == 3 ? 0 : m][q]];
+            }
+            if constexpr (DIM == 2) v[m] = F[at[m]];
+        }
+        if constexpr (DIM == 3) {
+#pragma unroll
+            for (int q = 0; q < kCPT0 + 4; ++q) z[q] = F[at[0] + oz[q]];
+        }
+#pragma unroll
+        for (int m = 0; m < kCPT0; ++m) {
+            g[m][0] = ((x[m][0] - x[m][3]) + 8.0 * (x[m][2] - x[m][1])) * c12[0];
+            g[m][1] = ((y[m][0] - y[m][3]) + 8.0 * (y[m][2] - y[m][1])) * c12[1];
+            g[m][2] = 0.0;
+            if constexpr (DIM == 3) {
+                g[m][2] = ((z[m] - z[m + 4]) + 8.0 * (z[m + 3] - z[m + 1])) * c12[2];
+                v[m] = z[m + 2];
+            }
+        }
+    }
+};
+
+// D = c lambda(R) / (kappa rho) once per level-0 cell, for grids with zero-flux faces: into
+// the residual array (free until the initial residual), where the face pass reads each face's
+// two D, or (start) the CG product vector, with the input check, for k_start.  Loads as in
+// k_moments.  256^3: 185 -> 180 us; 512 grids of 52.6 M cells: 530 us with the exact limiter's
+// tanh in the same kernel, 425 us without (128 against 148 registers).  A fourth wavefront a
+// SIMD in 3D (128 registers) spills: 207 us.
+template <int DIM, bool EXACT>
+__global__ void __launch_bounds__(kBlock)
+k_diffusion(const LevelDesc* __restrict__ L, GridState* __restrict__ S, JobList jl, const StepIO* __restrict__ io,
+            double c, int limiter, int start) {
+    const XcdOrder order(jl.total);
+    for (int k_ = order.first(); order.more(k_); k_ += order.per) {
+        const int t = order.tile(k_);
+        const int jb = find_job(jl.prefix, jl.njobs, t);
+        const LevelDesc& d = L[job_level(jl, jb)];
+        const StepIO& p = io[d.grid];
+        if (p.krd[0]) continue;                                  // diagonal-tensor D: in the face pass
+        const Grad4Cells<DIM> at(d, t - job_start(jl, jb));
+        const double c12[3] = {d.hinv[0] / 12.0, d.hinv[1] / 12.0, d.hinv[2] / 12.0};
+        double e[kCPT0], kk[kCPT0], g[kCPT0][3];
+#pragma unroll
+        for (int u = 0; u < kCPT0; ++u) kk[u] = as_global(p.kr)[at.at[u]];
+        at(p.E_in, c12, e, g);
+        const gptr<double> D = as_global(start ? d.Q : d.R);
+        bool bad = false;
+#pragma unroll
+        for (int u = 0; u < kCPT0; ++u) {
+            double g2 = g[u][0] * g[u][0] + g[u][1] * g[u][1];
+            if (DIM == 3) g2 += g[u][2] * g[u][2];
+            const double R = sqrt(g2) / (kk[u] * e[u]);
+            if (at.ok[u]) D[at.at[u]] = c * limiter_of<EXACT>(R, limiter) / kk[u];
+            bad = bad || !(e[u] > 0.0 && isfinite(e[u]) && kk[u] > 0.0 && isfinite(kk[u]));
+        }
+        // (a clamped cell is a cell of the grid)
+        if (start && bad) atomicOr(&S[d.sidx].bad, 1);
+    }
+}
+
+// The same where the plan has other faces (ghosts by kind): D once per level-0 cell,
 // stored in the level's residual array (free until the initial residual), so the face
 // pass reads each face's two D instead of recomputing the neighbour's stencil.  Grids
 // with a diagonal-tensor D compute theirs in the face pass.
-template <int DIM, bool BC>
+template <int DIM>
 __global__ void __launch_bounds__(kBlock)
 k_cell_D(const LevelDesc* __restrict__ L, JobList jl, const StepIO* __restrict__ io, double c, int limiter) {
     const XcdOrder order(jl.total);
@@ -515,7 +637,7 @@ k_cell_D(const LevelDesc* __restrict__ L, JobList jl, const StepIO* __restrict__
         const StepIO& p = io[d.grid];
         if (p.krd[0]) continue;                                  // uniform per tile
         const int lt = t - job_start(jl, jb);
-        const LevelDesc* gh = (BC && d.has_bc) ? &d : nullptr;
+        const LevelDesc* gh = d.has_bc ? &d : nullptr;
         const double c12[3] = {d.hinv[0] / 12.0, d.hinv[1] / 12.0, d.hinv[2] / 12.0};
 #pragma unroll
         for (int m_ = 0; m_ < kCPT0; ++m_) {
@@ -701,13 +823,6 @@ k_coarsen(const LevelDesc* __restrict__ L, JobList jl, int galerkin) {
 // (A x)_i = x_i + sum_faces w_f (x_i - x_nb); the residual is formed as
 // b - x - sum w (x - x_nb), so nearly equal neighbours cancel before scaling.
 // ---------------------------------------------------------------------------
-// Level arrays live in global memory, but pointers read from a LevelDesc carry no
-// address space, so accesses through them compile to flat loads and stores, which
-// also count against the LDS wait counter: a kernel that keeps global loads in
-// flight while it works on LDS must access them through global pointers.
-template <typename T> using gptr = __attribute__((address_space(1))) T*;
-template <typename T> __device__ __forceinline__ gptr<T> as_global(T* p) { return (gptr<T>)p; }
-
 template <typename T> struct Arr;
 template <> struct Arr<double> {
     __device__ static double* x(const LevelDesc& d) { return d.x; }
@@ -3184,71 +3299,6 @@ k_moments_bc(const LevelDesc* __restrict__ L, JobList jl, const MomentsIO* __res
     }
 }
 
-// The 4th-order gradient of a field with mirrored ghosts at a thread's kCPT0 cells of a
-// level-0 tile.  Every load is issued before the first use, from clamped cells.
-template <int DIM>
-struct Grad4Cells {
-    long at[kCPT0];              // flat index of each cell (clamped into the level)
-    bool ok[kCPT0];
-    // offsets of the neighbours -2, -1, +1, +2 (mirrored); the cells share their column of x
-    // (and in 3D of y)
-    int ox[4], oy[DIM == 3 ? 1 : kCPT0][4];
-    long oz[DIM == 3 ? kCPT0 + 4 : 1];   // 3D: a thread's cells are one column; planes k0 - 2 .. k0 + kCPT0 + 1
-
-    __device__ __forceinline__ Grad4Cells(const LevelDesc& d, int lt) {
-        const long sz = (long)d.n[0] * d.n[1];
-        int k0 = 0;
-#pragma unroll
-        for (int m = 0; m < kCPT0; ++m) {
-            int i, j, k;
-            at[m] = l0_cell<DIM>(d, lt, m, i, j, k, ok[m]);
-            if (m == 0) k0 = k;
-            const int t[4] = {-2, -1, 1, 2};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (m == 0) ox[q] = mirror(i + t[q], d.n[0]) - i;
-                if (m == 0 || DIM == 2) oy[DIM == 3 ? 0 : m][q] = (mirror(j + t[q], d.n[1]) - j) * d.n[0];
-            }
-        }
-        if constexpr (DIM == 3) {
-            // (the last planes of a column that runs past the level are not used)
-            const int n2 = d.n[2];
-#pragma unroll
-            for (int z = 0; z < kCPT0 + 4; ++z)
-                oz[z] = (min(max(mirror(k0 - 2 + z, n2), 0), n2 - 1) - k0) * sz;
-        }
-    }
-    // v: the field at the cells (3D: from the column); g: the gradient there
-    __device__ __forceinline__ void operator()(const double* F_, const double c12[3], double v[kCPT0],
-                                               double g[kCPT0][3]) const {
-        const gptr<const double> F = as_global(F_);
-        double x[kCPT0][4], y[kCPT0][4], z[DIM == 3 ? kCPT0 + 4 : 1];
-#pragma unroll
-        for (int m = 0; m < kCPT0; ++m) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                x[m][q] = F[at[m] + ox[q]];
-                y[m][q] = F[at[m] + oy[DIM == 3 ? 0 : m][q]];
-            }
-            if constexpr (DIM == 2) v[m] = F[at[m]];
-        }
-        if constexpr (DIM == 3) {
-#pragma unroll
-            for (int q = 0; q < kCPT0 + 4; ++q) z[q] = F[at[0] + oz[q]];
-        }
-#pragma unroll
-        for (int m = 0; m < kCPT0; ++m) {
-            g[m][0] = ((x[m][0] - x[m][3]) + 8.0 * (x[m][2] - x[m][1])) * c12[0];
-            g[m][1] = ((y[m][0] - y[m][3]) + 8.0 * (y[m][2] - y[m][1])) * c12[1];
-            g[m][2] = 0.0;
-            if constexpr (DIM == 3) {
-                g[m][2] = ((z[m] - z[m + 4]) + 8.0 * (z[m + 3] - z[m + 1])) * c12[2];
-                v[m] = z[m + 2];
-            }
-        }
-    }
-};
-
 // Plans with zero-flux faces: the same arithmetic with a tile's loads in flight together (one
 // field's stencil at a thread's four cells at a time, in 3D as a column that reads each
 // plane once) and through global pointers; the outputs, which nothing here reads again, past
@@ -3390,6 +3440,131 @@ k_residual(const LevelDesc* __restrict__ L, GridState* __restrict__ S, JobList j
         }
         tile_reduce_finish(d, S[d.sidx], lt, job_tiles(jl, jb), r2, unused, 1, fin, rtol,
                            max_cycles, sh, &flag);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Start of a step under CG on grids with zero-flux faces and one opacity: from each cell's D
+// (k_diffusion) the lower faces, b = X = E, the initial residual b - A E (the flows through
+// the cell's six faces; an upper face is formed as the neighbour forms it) and the partials
+// of ||b||^2, sum b (two a tile, in `part`) and ||r||^2 (in P[0], free until the first
+// iteration), in one pass: the separate face and residual passes read E, D and the faces
+// again.  zero_x: the V-cycle's level-0 iterate starts from memory.  256^3 in FP64: face and
+// residual passes 475 + 229 us, this 295 us (3.6 TB/s); 512 grids of 52.6 M cells: 1236 +
+// 619 us, this 870 us (3.4 TB/s).
+// ---------------------------------------------------------------------------
+template <int DIM, bool MIXED>
+__global__ void __launch_bounds__(kBlock)
+k_start(const LevelDesc* __restrict__ L, GridState* __restrict__ S, JobList jl, const StepIO* __restrict__ io,
+        int zero_x, int fin, double rtol, int max_cycles) {
+    __shared__ double sh[2 * kBlock / 64];
+    __shared__ int flag;
+    const XcdOrder order(jl.total);
+    for (int k_ = order.first(); order.more(k_); k_ += order.per) {
+        const int t = order.tile(k_);
+        const int jb = find_job(jl.prefix, jl.njobs, t);
+        const LevelDesc& d = L[job_level(jl, jb)];
+        const int lt = t - job_start(jl, jb), nt = job_tiles(jl, jb);
+        const StepIO& p = io[d.grid];
+        const double dt = p.dt;
+        const gptr<const double> D = as_global((const double*)d.Q), E = as_global(p.E_in);
+        const int n0 = d.n[0], n1 = d.n[1], n2 = d.n[2];
+        const long sz = (long)n0 * n1;
+        long at[kCPT0];
+        bool ok[kCPT0], yl[kCPT0], yu[kCPT0], xl = false, xu = false;
+        // D and E of each cell and its x and y neighbours; in 3D the cells' column and the
+        // planes below and above it
+        double Dc[kCPT0 + 2], Ec[kCPT0 + 2], Dx[kCPT0][2], Ex[kCPT0][2], Dy[kCPT0][2], Ey[kCPT0][2];
+        int k0 = 0;
+#pragma unroll
+        for (int m = 0; m < kCPT0; ++m) {
+            int i, j, k;
+            at[m] = l0_cell<DIM>(d, lt, m, i, j, k, ok[m]);
+            if (m == 0) k0 = k;
+            xl = i > 0;
+            xu = i + 1 < n0;
+            yl[m] = j > 0;
+            yu[m] = j + 1 < n1;
+            const long c = at[m], l = xl ? c - 1 : c, r = xu ? c + 1 : c, b = yl[m] ? c - n0 : c, f = yu[m] ? c + n0 : c;
+            Dc[m + 1] = D[c];
+            Ec[m + 1] = E[c];
+            Dx[m][0] = D[l];
+            Dx[m][1] = D[r];
+            Dy[m][0] = D[b];
+            Dy[m][1] = D[f];
+            Ex[m][0] = E[l];
+            Ex[m][1] = E[r];
+            Ey[m][0] = E[b];
+            Ey[m][1] = E[f];
+        }
+        if constexpr (DIM == 3) {
+            const long b = k0 > 0 ? at[0] - sz : at[0], f = k0 + kCPT0 < n2 ? at[kCPT0 - 1] + sz : at[kCPT0 - 1];
+            Dc[0] = D[b];
+            Ec[0] = E[b];
+            Dc[kCPT0 + 1] = D[f];
+            Ec[kCPT0 + 1] = E[f];
+        }
+        double s2 = 0.0, s1 = 0.0, r2 = 0.0, unused = 0.0;
+        double wzl = 0.0;                                      // the face below the next cell of the column
+        if (DIM == 3 && k0 > 0) wzl = face_w(Dc[0], Dc[1], dt, d.hinv[2]);
+#pragma unroll
+        for (int m = 0; m < kCPT0; ++m) {
+            const double Dm = Dc[m + 1], e = Ec[m + 1];
+            const double wl = xl ? face_w(Dx[m][0], Dm, dt, d.hinv[0]) : 0.0;
+            const double wr = xu ? face_w(Dm, Dx[m][1], dt, d.hinv[0]) : 0.0;
+            const double wd = yl[m] ? face_w(Dy[m][0], Dm, dt, d.hinv[1]) : 0.0;
+            const double wu = yu[m] ? face_w(Dm, Dy[m][1], dt, d.hinv[1]) : 0.0;
+            double r = e - e;
+            r -= wl * (e - Ex[m][0]);
+            r -= wr * (e - Ex[m][1]);
+            r -= wd * (e - Ey[m][0]);
+            r -= wu * (e - Ey[m][1]);
+            double wb = 0.0;
+            if constexpr (DIM == 3) {
+                wb = wzl;
+                const double wf = k0 + m + 1 < n2 ? face_w(Dm, Dc[m + 2], dt, d.hinv[2]) : 0.0;
+                r -= wb * (e - Ec[m]);
+                r -= wf * (e - Ec[m + 2]);
+                wzl = wf;
+            }
+            if (!ok[m]) continue;
+            const long c = at[m];
+            as_global(d.w[0])[c] = wl;
+            as_global(d.w[1])[c] = wd;
+            if (DIM == 3) as_global(d.w[2])[c] = wb;
+            as_global(d.B0)[c] = e;
+            as_global(d.X)[c] = e;
+            as_global(d.R)[c] = r;
+            if (MIXED) {
+                as_global(d.w32[0])[c] = (float)wl;
+                as_global(d.w32[1])[c] = (float)wd;
+                if (DIM == 3) as_global(d.w32[2])[c] = (float)wb;
+                as_global(d.b32)[c] = (float)r;
+                if (zero_x) as_global(d.x32)[c] = 0.0f;
+            } else if (zero_x) {
+                as_global(d.x)[c] = 0.0;
+            }
+            s2 += e * e;
+            s1 += e;
+            r2 += r * r;
+        }
+        GridState& g = S[d.sidx];
+        double* const part2 = d.P[0];
+        block_sum2<kBlock>(s2, s1, sh);
+        block_sum2<kBlock>(r2, unused, sh);
+        if (threadIdx.x == 0) {
+            d.part[2 * lt] = s2;
+            d.part[2 * lt + 1] = s1;
+            part2[lt] = r2;
+        }
+        if (!fin) continue;                                    // a k_finalize launch finishes
+        if (!grid_tile_done(g, nt, &flag)) continue;
+        sum_parts_coherent(d.part, nt, 2, s2, s1, sh);
+        sum_parts_coherent(part2, nt, 1, r2, unused, sh);
+        if (threadIdx.x == 0) {
+            finalize_grid(g, s2, s1, FIN_B, rtol, max_cycles);
+            if (g.active) finalize_grid(g, r2, 0.0, FIN_R_INIT, rtol, max_cycles);
+        }
     }
 }
 
@@ -4041,6 +4216,14 @@ Acct* acct_get() { return t_acct; }
 #define FLD_DISPATCH_DIM(dim, ...) \
     do { if ((dim) == 3) { constexpr int D = 3; __VA_ARGS__; } else { constexpr int D = 2; __VA_ARGS__; } } while (0)
 
+template <int DIM>
+static void diffusion(const LevelDesc* L, GridState* S, JobList jl, const StepIO* io, double c, int limiter,
+                      int start, int g, hipStream_t s) {
+    if (limiter == FLD_LIMITER_LP_EXACT)
+        hipLaunchKernelGGL((k_diffusion<DIM, true>), dim3(g), dim3(kBlock), 0, s, L, S, jl, io, c, limiter, start);
+    else hipLaunchKernelGGL((k_diffusion<DIM, false>), dim3(g), dim3(kBlock), 0, s, L, S, jl, io, c, limiter, start);
+}
+
 void launch_coeff(int dim, bool mixed, int bc, const LevelDesc* L, GridState* S, JobList jl,
                   const StepIO* io, double c, int limiter, int fin, double rtol, int max_cycles, int nblk,
                   hipStream_t s) {
@@ -4050,12 +4233,28 @@ void launch_coeff(int dim, bool mixed, int bc, const LevelDesc* L, GridState* S,
     const int g = blocks_for_xcd(jl.total, nblk);
 #define FLD_COEFF(M, B) hipLaunchKernelGGL((k_coeff<D, M, B>), dim3(g), dim3(kBlock), 0, s, L, S, jl, io, c, limiter, fin, rtol, max_cycles)
     FLD_DISPATCH_DIM(dim, {
-        if (bc) hipLaunchKernelGGL((k_cell_D<D, true>), dim3(g), dim3(kBlock), 0, s, L, jl, io, c, limiter);
-        else hipLaunchKernelGGL((k_cell_D<D, false>), dim3(g), dim3(kBlock), 0, s, L, jl, io, c, limiter);
+        if (bc) hipLaunchKernelGGL((k_cell_D<D>), dim3(g), dim3(kBlock), 0, s, L, jl, io, c, limiter);
+        else diffusion<D>(L, S, jl, io, c, limiter, 0, g, s);
         if (bc) { if (mixed) FLD_COEFF(true, true); else FLD_COEFF(false, true); }
         else { if (mixed) FLD_COEFF(true, false); else FLD_COEFF(false, false); }
     });
 #undef FLD_COEFF
+}
+
+void launch_start(int dim, bool mixed, const LevelDesc* L, GridState* S, JobList jl, const StepIO* io, double c,
+                  int limiter, int zero_x, int fin, double rtol, int max_cycles, int nblk, hipStream_t s) {
+    if (jl.total <= 0) return;
+    // D pass: E, kappa rho read, D written; then E, D read, faces, b, x, r written (mixed: the
+    // FP32 faces and right-hand side), the V-cycle's iterate zeroed where it is read
+    if (acct_add(jl.cells * (8.0 * 3 + 8.0 * (5 + dim) + (mixed ? 4.0 * (dim + 1) : 0.0) +
+                             (zero_x ? (mixed ? 4.0 : 8.0) : 0.0))))
+        return;
+    const int g = blocks_for_xcd(jl.total, nblk);
+    FLD_DISPATCH_DIM(dim, {
+        diffusion<D>(L, S, jl, io, c, limiter, 1, g, s);
+        if (mixed) hipLaunchKernelGGL((k_start<D, true>), dim3(g), dim3(kBlock), 0, s, L, S, jl, io, zero_x, fin, rtol, max_cycles);
+        else hipLaunchKernelGGL((k_start<D, false>), dim3(g), dim3(kBlock), 0, s, L, S, jl, io, zero_x, fin, rtol, max_cycles);
+    });
 }
 
 void launch_finalize(const LevelDesc* L, GridState* S, JobList jl, int mode, double rtol,

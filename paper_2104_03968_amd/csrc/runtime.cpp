@@ -1154,11 +1154,27 @@ int plan_upload_io(Plan& p, const StepIO* io, hipStream_t s) {
     return FLD_OK;
 }
 
-int plan_prologue(Plan& p, hipStream_t s) {
+// Whether the V-cycle reads level 0's iterate where it starts from zero: the per-colour sweeps,
+// and the direct solve of a grid that has no other level.
+static bool iterate_read(const Plan& p, const DimLists& D) {
+    bool solved = false;
+    for (int32_t li : D.coarsest.levels) solved = solved || p.levels[li].level == 0;
+    return solved || level0_reads_iterate(p, D);
+}
+
+int plan_prologue(Plan& p, hipStream_t s, bool tensor) {
     const int zero_x = (p.krylov || p.mixed) ? 1 : 0;
     for (auto& D : p.dl) {
         if (D.l0_cell.empty()) continue;
         const JobList& l0 = D.l0_cell.dev;
+        if (p.krylov && !p.any_bc && !tensor) {
+            launch_start(D.dim, p.mixed, p.dL, p.dS, l0, p.dIO, p.opts.c, p.opts.limiter, iterate_read(p, D), D.fin_fused,
+                         p.opts.rtol, p.opts.max_cycles, cell_blocks(p), s);
+            if (!D.fin_fused) launch_finalize(p.dL, p.dS, l0, FIN_START, p.opts.rtol, p.opts.max_cycles, s);
+            for (auto& c : D.coarsen)
+                launch_coarsen(D.dim, p.mixed, p.dL, c.dev, p.opts.coarse_op == FLD_COARSE_GALERKIN, p.nblk, s);
+            continue;
+        }
         launch_coeff(D.dim, p.mixed, p.any_bc, p.dL, p.dS, l0, p.dIO, p.opts.c, p.opts.limiter, D.fin_fused ? FIN_B : -1,
                      p.opts.rtol, p.opts.max_cycles, cell_blocks(p), s);
         if (!D.fin_fused) launch_finalize(p.dL, p.dS, l0, FIN_B, p.opts.rtol, p.opts.max_cycles, s);
@@ -1222,7 +1238,7 @@ static int step(Plan& p, const double* const* E_in, const double* const* kr, dou
     }
     int rc = plan_upload_io(p, io.data(), s);
     if (rc != FLD_OK) return rc;
-    if ((rc = plan_prologue(p, s)) != FLD_OK) return rc;
+    if ((rc = plan_prologue(p, s, krd != nullptr)) != FLD_OK) return rc;
     // V-cycles in rounds: each round replays `burst` cycles, then reads back how
     // many grids are still active.  The first burst is sized from the previous
     // step's cycle count so a typical step needs one or two host round trips.
