@@ -311,7 +311,7 @@ struct ImexIO {
 };
 
 struct Control {
-    int32_t nactive;     // grids still iterating after the last count
+    int32_t pad0_;       // (bad_exchange and bisected are cleared in one copy)
     int32_t bad_exchange;
     int64_t bisected;    // exchange cells that used the bisection fallback
     int32_t bad_imex;    // an IMEX stage met an invalid cell
@@ -399,13 +399,17 @@ void launch_tail(int dim, bool fp32, int bc, const LevelDesc* L, const GridState
                  int cpc, int nu1, int nu2, int plain64, hipStream_t s);
 // cpc: cells of one colour of the first level a thread holds (1 or 2).
 constexpr size_t kTailLdsBudget = 150 * 1024;
-// select: 0 = active grids, 1 = inactive grids whose status is FLD_OK (convergence check).
+// select: 0 = active grids, 1 = inactive grids whose status is FLD_OK (convergence check),
+// 2 = active grids at iteration 0 (sent back to iterate by a check).
 // zero_x: also clear the level-0 V-cycle iterate (FP64 or FP32 by `mixed`); mixed also
 // writes the FP32 right-hand side.
 // fin: FinMode applied by the block that finishes a grid's last tile (-1: none;
 // a separate launch_finalize finishes the reduction).
 void launch_residual(int dim, bool mixed, const LevelDesc* L, GridState* S, JobList jl,
                      int select, int zero_x, int fin, double rtol, int max_cycles, int nblk, hipStream_t s);
+// Convergence check of the grids that stopped with FLD_OK: the norm alone, the iterate to E_out.
+void launch_check(int dim, const LevelDesc* L, GridState* S, JobList jl, const StepIO* io, int fin, double rtol,
+                  int max_cycles, int nblk, hipStream_t s);
 void launch_cg_rz(int dim, bool mixed, const LevelDesc* L, GridState* S, JobList jl, int fin, double rtol,
                   int max_cycles, int nblk, hipStream_t s);
 void launch_cg_pq(int dim, bool mixed, const LevelDesc* L, GridState* S, JobList jl, int fin, double rtol,
@@ -423,7 +427,6 @@ void launch_correct(int dim, bool mixed, const LevelDesc* L, const GridState* S,
                     hipStream_t s);
 void launch_output(int dim, const LevelDesc* L, JobList jl, const StepIO* io, int nblk,
                    hipStream_t s);
-void launch_count(const GridState* S, int ngrids, Control* ctrl, hipStream_t s);
 // Radiation moments of every level-0 cell of the listed grids (io indexed by grid).
 // bc: the plan has faces other than zero flux.
 void launch_moments(int dim, int bc, const LevelDesc* L, JobList jl, const MomentsIO* io, double c, int limiter,

@@ -1202,6 +1202,25 @@ void plan_verify(Plan& p, hipStream_t s) {
     }
 }
 
+// The same at the end of a step, with the iterate of the grids checked to their outputs; R and
+// the V-cycle's iterate stay, so a grid that is sent back needs a plan_restart first.
+static void plan_check(Plan& p, hipStream_t s) {
+    for (auto& D : p.dl) {
+        if (D.l0_cell.empty()) continue;
+        launch_check(D.dim, p.dL, p.dS, D.l0_cell.dev, p.dIO, D.fin_fused ? FIN_R_VERIFY : -1, p.opts.rtol,
+                     p.opts.max_cycles, cell_blocks(p), s);
+        if (!D.fin_fused)
+            launch_finalize(p.dL, p.dS, D.l0_cell.dev, FIN_R_VERIFY, p.opts.rtol, p.opts.max_cycles, s);
+    }
+}
+
+static void plan_restart(Plan& p, hipStream_t s) {
+    for (auto& D : p.dl)
+        if (!D.l0_cell.empty())
+            launch_residual(D.dim, p.mixed, p.dL, p.dS, D.l0_cell.dev, 2, 1, -1, p.opts.rtol, p.opts.max_cycles,
+                            cell_blocks(p), s);
+}
+
 void plan_output(Plan& p, hipStream_t s) {
     for (auto& D : p.dl) {
         if (D.l0_cell.empty()) continue;
@@ -1250,6 +1269,9 @@ static int step(Plan& p, const double* const* E_in, const double* const* kr, dou
         done = 1;
     }
     int burst = std::max(1, std::min(p.last_cycles > 0 ? p.last_cycles - done : 4, p.opts.max_cycles - done));
+    // whether every output is written and every state is on the host (one wait for a step that
+    // ends as it should)
+    bool complete = false;
     while (done < p.opts.max_cycles) {
         const int nrun = std::min(burst, p.opts.max_cycles - done);
         for (int r = 0; r < nrun; ++r) {
@@ -1261,16 +1283,30 @@ static int step(Plan& p, const double* const* E_in, const double* const* kr, dou
         // CG stops on its recursive residual: the grids that stopped are confirmed on the
         // true FP64 residual in the same round trip (a grid that misses the target
         // restarts; grids still iterating are not touched)
-        if (p.krylov) plan_verify(p, s);
-        launch_count(p.dS, G, p.dCtrl, s);
-        FLD_HIP(hipMemcpyAsync(p.hCtrl, p.dCtrl, sizeof(Control), hipMemcpyDeviceToHost, s));
+        if (p.krylov) plan_check(p, s);
+        FLD_HIP(hipGetLastError());
+        FLD_HIP(hipMemcpyAsync(p.hS, p.dS, G * sizeof(GridState), hipMemcpyDeviceToHost, s));
         FLD_HIP(hipStreamSynchronize(s));
-        if (p.hCtrl->nactive == 0) break;
+        bool active = false, back = false, ok = true;
+        for (int g = 0; g < G; ++g) {
+            const GridState& st = p.hS[g];
+            active = active || st.active;
+            back = back || (st.active && st.iter == 0);
+            ok = ok && st.status == FLD_OK;
+        }
+        if (!active) {
+            complete = p.krylov && ok;
+            break;
+        }
+        if (p.krylov && back && done < p.opts.max_cycles) plan_restart(p, s);
         burst = std::max(1, burst / 2);
     }
-    plan_output(p, s);
-    FLD_HIP(hipMemcpyAsync(p.hS, p.dS, G * sizeof(GridState), hipMemcpyDeviceToHost, s));
-    FLD_HIP(hipStreamSynchronize(s));
+    if (!complete) {
+        plan_output(p, s);
+        FLD_HIP(hipGetLastError());
+        FLD_HIP(hipMemcpyAsync(p.hS, p.dS, G * sizeof(GridState), hipMemcpyDeviceToHost, s));
+        FLD_HIP(hipStreamSynchronize(s));
+    }
     rc = FLD_OK;
     int maxc = 0;
     for (int g = 0; g < G; ++g) {
