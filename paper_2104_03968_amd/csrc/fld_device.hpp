@@ -335,6 +335,8 @@ void launch_finalize(const LevelDesc* L, GridState* S, JobList jl, int mode, dou
                      int max_cycles, hipStream_t s);
 // galerkin: coarse weights of R A P (piecewise-constant P, child-mean R); 0: rediscretised.
 void launch_coarsen(int dim, bool mixed, const LevelDesc* L, JobList jl, int galerkin, int nblk, hipStream_t s);
+// From the first level of each grid's tail (list: those) down.
+void launch_coarsen_tail(int dim, bool mixed, const LevelDesc* L, JobList jl, int galerkin, hipStream_t s);
 void launch_smooth(int dim, bool fp32, const LevelDesc* L, const GridState* S, JobList jl,
                    int color, int nblk, hipStream_t s);
 void launch_restrict(int dim, bool fp32, const LevelDesc* L, const GridState* S, JobList jl,

@@ -41,9 +41,9 @@ struct DimLists {
     int dim = 0;
     HostList l0_cell;                          // level 0, cell tiles
     std::vector<HostList> smooth;              // per depth, smoother tiles
-    std::vector<HostList> restrict_;           // per depth, cell tiles of the coarse level
+    std::vector<HostList> restrict_;           // per depth, cell tiles of the coarse level (restriction and
+                                               // operator coarsening)
     std::vector<HostList> prolong;             // per depth, cell tiles of the fine level
-    std::vector<HostList> coarsen;             // per depth, all levels with a coarser one
     std::vector<HostList> down2, up2;          // per depth, fused 2D tiles (same levels as smooth)
     std::vector<int> thr_dn, thr_up;           // per depth, workgroup size of those tiles (256 or 1024)
     std::vector<HostList> mdn, mup;            // per depth, row-marching windows (same levels)
@@ -220,6 +220,7 @@ int plan_init(Plan& p, const fld_grid* grids, int ngrids, const fld_opts& opts);
 int plan_bind(Plan& p, void* dev, size_t bytes, const GridState* init);
 // Per-step phases, asynchronous on s (the StepIO table must be on the device).
 // (tensor: the step gives one opacity per direction)
+void plan_coarsen(Plan& p, const DimLists& D, hipStream_t s);   // the coarse levels' operators
 int plan_prologue(Plan& p, hipStream_t s, bool tensor = false);   // coefficients, norms, initial residual
 void plan_cycle(Plan& p, hipStream_t s);                 // one V-cycle (+ CG update) for active grids
 void plan_verify(Plan& p, hipStream_t s);                // true residual of grids CG reported converged

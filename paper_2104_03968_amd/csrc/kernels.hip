@@ -768,6 +768,46 @@ k_coeff(const LevelDesc* __restrict__ L, GridState* __restrict__ S, JobList jl,
 // 2^DIM (faces inside a coarse cell cancel), twice the rediscretised weight.
 // ---------------------------------------------------------------------------
 template <int DIM, bool MIXED>
+__device__ __forceinline__ void coarsen_cell(const LevelDesc& f, const LevelDesc& cL, int I, int J, int K, int galerkin) {
+    const long cidx = I + (long)cL.n[0] * (J + (long)cL.n[1] * K);
+    const long fsy = f.n[0], fsz = (long)f.n[0] * f.n[1];
+    const long f0 = 2 * I + 2 * J * fsy + (DIM == 3 ? 2 * K * fsz : 0);
+    // 1/2^(DIM-1) * 1/4, or 1/2^DIM for the Galerkin product
+    const double sc = galerkin ? ((DIM == 3) ? 0.125 : 0.25) : ((DIM == 3) ? 0.0625 : 0.125);
+    double wc[3] = {0.0, 0.0, 0.0};
+    // x faces: sub-faces at fine x = 2I over (j, j+1) [and (k, k+1)]
+    const int pm = f.per_mask;                        // periodic: the wrap faces coarsen too
+    if (I > 0 || (pm & 1)) {
+        double s = f.w[0][f0] + f.w[0][f0 + fsy];
+        if (DIM == 3) s += f.w[0][f0 + fsz] + f.w[0][f0 + fsy + fsz];
+        wc[0] = s * sc;
+    }
+    if (J > 0 || (pm & 2)) {
+        double s = f.w[1][f0] + f.w[1][f0 + 1];
+        if (DIM == 3) s += f.w[1][f0 + fsz] + f.w[1][f0 + 1 + fsz];
+        wc[1] = s * sc;
+    }
+    if (DIM == 3 && (K > 0 || (pm & 4))) {
+        wc[2] = (f.w[2][f0] + f.w[2][f0 + 1] + f.w[2][f0 + fsy] + f.w[2][f0 + 1 + fsy]) * sc;
+    }
+    for (int a = 0; a < DIM; ++a) {
+        cL.w[a][cidx] = wc[a];
+        if (MIXED) cL.w32[a][cidx] = (float)wc[a];
+    }
+    // Dirichlet couplings: the 2^(DIM-1) children on a face carry alpha each; the
+    // rediscretised coarse coupling is their mean over 4 (ghost two fine widths away),
+    // the Galerkin one their sum over 2^DIM
+    if (cL.ad) {
+        const double* a = f.ad;
+        double sa = a[f0] + a[f0 + 1] + a[f0 + fsy] + a[f0 + fsy + 1];
+        if (DIM == 3) sa += a[f0 + fsz] + a[f0 + fsz + 1] + a[f0 + fsz + fsy] + a[f0 + fsz + fsy + 1];
+        const double ac = sa * (galerkin ? ((DIM == 3) ? 0.125 : 0.25) : ((DIM == 3) ? 0.0625 : 0.125));
+        cL.ad[cidx] = ac;
+        if (MIXED) cL.ad32[cidx] = (float)ac;
+    }
+}
+
+template <int DIM, bool MIXED>
 __global__ void __launch_bounds__(kBlock)
 k_coarsen(const LevelDesc* __restrict__ L, JobList jl, int galerkin) {
     const XcdOrder order(jl.total);
@@ -779,42 +819,25 @@ k_coarsen(const LevelDesc* __restrict__ L, JobList jl, int galerkin) {
         int I, J, K;
         cell_of_tile<DIM>(cL.n, t - job_start(jl, jb), threadIdx.x, I, J, K);
         if (I >= cL.n[0] || J >= cL.n[1]) continue;
-        const long cidx = I + (long)cL.n[0] * (J + (long)cL.n[1] * K);
-        const long fsy = f.n[0], fsz = (long)f.n[0] * f.n[1];
-        const long f0 = 2 * I + 2 * J * fsy + (DIM == 3 ? 2 * K * fsz : 0);
-        // 1/2^(DIM-1) * 1/4, or 1/2^DIM for the Galerkin product
-        const double sc = galerkin ? ((DIM == 3) ? 0.125 : 0.25) : ((DIM == 3) ? 0.0625 : 0.125);
-        double wc[3] = {0.0, 0.0, 0.0};
-        // x faces: sub-faces at fine x = 2I over (j, j+1) [and (k, k+1)]
-        const int pm = f.per_mask;                        // periodic: the wrap faces coarsen too
-        if (I > 0 || (pm & 1)) {
-            double s = f.w[0][f0] + f.w[0][f0 + fsy];
-            if (DIM == 3) s += f.w[0][f0 + fsz] + f.w[0][f0 + fsy + fsz];
-            wc[0] = s * sc;
+        coarsen_cell<DIM, MIXED>(f, cL, I, J, K, galerkin);
+    }
+}
+
+// The same from the first level of each grid's tail down to its coarsest, one workgroup a grid:
+// a launch a level took 3 us each (with the gap to the next 4) for at most 1024 cells.  64^2:
+// five launches a step were 14 us and their gaps, two are 8 us (step 166 -> 157 us).
+template <int DIM, bool MIXED>
+__global__ void __launch_bounds__(kTailThreads)
+k_coarsen_tail(const LevelDesc* __restrict__ L, JobList jl, int galerkin) {
+    for (int li = job_level(jl, blockIdx.x); L[li].coarse >= 0; li = L[li].coarse) {
+        const LevelDesc& f = L[li];
+        const LevelDesc& cL = L[f.coarse];
+        const int n0 = cL.n[0], n1 = cL.n[1], n = n0 * n1 * cL.n[2];
+        for (int q = threadIdx.x; q < n; q += kTailThreads) {
+            const int r = q / n0;
+            coarsen_cell<DIM, MIXED>(f, cL, q - r * n0, DIM == 3 ? r % n1 : r, DIM == 3 ? r / n1 : 0, galerkin);
         }
-        if (J > 0 || (pm & 2)) {
-            double s = f.w[1][f0] + f.w[1][f0 + 1];
-            if (DIM == 3) s += f.w[1][f0 + fsz] + f.w[1][f0 + 1 + fsz];
-            wc[1] = s * sc;
-        }
-        if (DIM == 3 && (K > 0 || (pm & 4))) {
-            wc[2] = (f.w[2][f0] + f.w[2][f0 + 1] + f.w[2][f0 + fsy] + f.w[2][f0 + 1 + fsy]) * sc;
-        }
-        for (int a = 0; a < DIM; ++a) {
-            cL.w[a][cidx] = wc[a];
-            if (MIXED) cL.w32[a][cidx] = (float)wc[a];
-        }
-        // Dirichlet couplings: the 2^(DIM-1) children on a face carry alpha each; the
-        // rediscretised coarse coupling is their mean over 4 (ghost two fine widths away),
-        // the Galerkin one their sum over 2^DIM
-        if (cL.ad) {
-            const double* a = f.ad;
-            double sa = a[f0] + a[f0 + 1] + a[f0 + fsy] + a[f0 + fsy + 1];
-            if (DIM == 3) sa += a[f0 + fsz] + a[f0 + fsz + 1] + a[f0 + fsz + fsy] + a[f0 + fsz + fsy + 1];
-            const double ac = sa * (galerkin ? ((DIM == 3) ? 0.125 : 0.25) : ((DIM == 3) ? 0.0625 : 0.125));
-            cL.ad[cidx] = ac;
-            if (MIXED) cL.ad32[cidx] = (float)ac;
-        }
+        __syncthreads();
     }
 }
 
@@ -4273,6 +4296,16 @@ void launch_coarsen(int dim, bool mixed, const LevelDesc* L, JobList jl, int gal
     FLD_DISPATCH_DIM(dim, {
         if (mixed) hipLaunchKernelGGL((k_coarsen<D, true>), dim3(g), dim3(kBlock), 0, s, L, jl, galerkin);
         else hipLaunchKernelGGL((k_coarsen<D, false>), dim3(g), dim3(kBlock), 0, s, L, jl, galerkin);
+    });
+}
+
+void launch_coarsen_tail(int dim, bool mixed, const LevelDesc* L, JobList jl, int galerkin, hipStream_t s) {
+    if (jl.total <= 0) return;
+    // (the levels below the first add 1 / (2^dim - 1) to its cells)
+    if (acct_add(jl.cells * (8.0 * dim + (mixed ? 4.0 * dim : 8.0 * dim) / (1 << dim)) * (1 << dim) / ((1 << dim) - 1))) return;
+    FLD_DISPATCH_DIM(dim, {
+        if (mixed) hipLaunchKernelGGL((k_coarsen_tail<D, true>), dim3(jl.total), dim3(kTailThreads), 0, s, L, jl, galerkin);
+        else hipLaunchKernelGGL((k_coarsen_tail<D, false>), dim3(jl.total), dim3(kTailThreads), 0, s, L, jl, galerkin);
     });
 }
 

@@ -483,20 +483,6 @@ static void build_lists(Plan& p) {
             r.prefix.assign(1, 0);
             for (int32_t li : r.levels) r.prefix.push_back(r.prefix.back() + cell_tiles(p.levels[p.levels[li].coarse].n));
         }
-        // coarse face weights are needed on every level, tails included
-        D.coarsen.resize(0);
-        int depth_all = 0;
-        for (int g = 0; g < p.ngrids(); ++g)
-            if (p.grids[g].ndim == D.dim) depth_all = std::max(depth_all, p.nlev[g] - 1);
-        D.coarsen.resize(depth_all);
-        for (int g = 0; g < p.ngrids(); ++g) {
-            if (p.grids[g].ndim != D.dim) continue;
-            for (int dpt = 0; dpt < p.nlev[g] - 1; ++dpt) D.coarsen[dpt].levels.push_back(p.level0[g] + dpt);
-        }
-        for (auto& c : D.coarsen) {
-            c.prefix.assign(1, 0);
-            for (int32_t li : c.levels) c.prefix.push_back(c.prefix.back() + cell_tiles(p.levels[p.levels[li].coarse].n));
-        }
     }
 }
 
@@ -582,7 +568,6 @@ static void layout(Plan& p) {
         place_list(D.rz3);
         place_list(D.coarsest);
         place_list(D.tail);
-        for (auto& l : D.coarsen) place_list(l);
         for (auto& l : D.down2) place_list(l);
         for (auto& l : D.up2) place_list(l);
         for (auto& l : D.mdn) place_list(l);
@@ -1109,7 +1094,7 @@ int plan_bind(Plan& p, void* dev, size_t bytes, const GridState* init) {
         stage_list(p, D.rz3, img);
         stage_list(p, D.coarsest, img);
         stage_list(p, D.tail, img);
-        for (auto* v : {&D.coarsen, &D.down2, &D.up2, &D.mdn, &D.mup, &D.sw3, &D.sr3, &D.m3, &D.tl[0], &D.tl[1], &D.tl[2],
+        for (auto* v : {&D.down2, &D.up2, &D.mdn, &D.mup, &D.sw3, &D.sr3, &D.m3, &D.tl[0], &D.tl[1], &D.tl[2],
                         &D.smooth, &D.restrict_, &D.prolong, &D.tail_from, &D.coarsest_from})
             for (auto& l : *v) stage_list(p, l, img);
         if (!D.tail.empty() && prepare_tail(D.dim, p.mixed, D.tail_smem) != 0) {
@@ -1154,6 +1139,13 @@ int plan_upload_io(Plan& p, const StepIO* io, hipStream_t s) {
     return FLD_OK;
 }
 
+// Level by level where a level's cells fill the card, the tails' levels in one launch.
+void plan_coarsen(Plan& p, const DimLists& D, hipStream_t s) {
+    const int galerkin = p.opts.coarse_op == FLD_COARSE_GALERKIN;
+    for (auto& c : D.restrict_) launch_coarsen(D.dim, p.mixed, p.dL, c.dev, galerkin, p.nblk, s);
+    launch_coarsen_tail(D.dim, p.mixed, p.dL, D.tail.dev, galerkin, s);
+}
+
 // Whether the V-cycle reads level 0's iterate where it starts from zero: the per-colour sweeps,
 // and the direct solve of a grid that has no other level.
 static bool iterate_read(const Plan& p, const DimLists& D) {
@@ -1171,15 +1163,13 @@ int plan_prologue(Plan& p, hipStream_t s, bool tensor) {
             launch_start(D.dim, p.mixed, p.dL, p.dS, l0, p.dIO, p.opts.c, p.opts.limiter, iterate_read(p, D), D.fin_fused,
                          p.opts.rtol, p.opts.max_cycles, cell_blocks(p), s);
             if (!D.fin_fused) launch_finalize(p.dL, p.dS, l0, FIN_START, p.opts.rtol, p.opts.max_cycles, s);
-            for (auto& c : D.coarsen)
-                launch_coarsen(D.dim, p.mixed, p.dL, c.dev, p.opts.coarse_op == FLD_COARSE_GALERKIN, p.nblk, s);
+            plan_coarsen(p, D, s);
             continue;
         }
         launch_coeff(D.dim, p.mixed, p.any_bc, p.dL, p.dS, l0, p.dIO, p.opts.c, p.opts.limiter, D.fin_fused ? FIN_B : -1,
                      p.opts.rtol, p.opts.max_cycles, cell_blocks(p), s);
         if (!D.fin_fused) launch_finalize(p.dL, p.dS, l0, FIN_B, p.opts.rtol, p.opts.max_cycles, s);
-        for (auto& c : D.coarsen)
-            launch_coarsen(D.dim, p.mixed, p.dL, c.dev, p.opts.coarse_op == FLD_COARSE_GALERKIN, p.nblk, s);
+        plan_coarsen(p, D, s);
         launch_residual(D.dim, p.mixed, p.dL, p.dS, l0, 0, zero_x, D.fin_fused ? FIN_R_INIT : -1, p.opts.rtol,
                         p.opts.max_cycles, cell_blocks(p), s);
         if (!D.fin_fused) launch_finalize(p.dL, p.dS, l0, FIN_R_INIT, p.opts.rtol, p.opts.max_cycles, s);
@@ -1856,8 +1846,7 @@ int32_t fld_coefficients(fld_plan_t plan, const double* const* E_in, const doubl
                               D.fin_fused ? fld::FIN_B : -1, p.opts.rtol, p.opts.max_cycles, fld::cell_blocks(p), s);
             if (!D.fin_fused)
                 fld::launch_finalize(p.dL, p.dS, D.l0_cell.dev, fld::FIN_B, p.opts.rtol, p.opts.max_cycles, s);
-            for (auto& c : D.coarsen)
-                fld::launch_coarsen(D.dim, p.mixed, p.dL, c.dev, p.opts.coarse_op == FLD_COARSE_GALERKIN, p.nblk, s);
+            fld::plan_coarsen(p, D, s);
         }
         FLD_HIP(hipGetLastError());
         FLD_HIP(hipStreamSynchronize(s));            // staging buffer free on return
