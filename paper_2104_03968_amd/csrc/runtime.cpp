@@ -654,6 +654,7 @@ static void layout(Plan& p) {
     for (size_t li = 0; li < NL; ++li) {
         const LevelDesc& d = p.levels[li];
         if (!p.nb_bc() || !p.dl[d.ndim - 2].tile || d.coarse < 0) continue;
+        if (p.tail_lev[d.grid] >= 0 && d.level >= p.tail_lev[d.grid]) continue;   // the tail has no second iterate
         p.foff[li].opt_xs = true;
         if (d.level == 0) continue;
         p.foff[li].xs = off;
