@@ -351,8 +351,9 @@ void launch_restrict_rhs(int dim, bool fp32, const LevelDesc* L, const GridState
                          int nblk, hipStream_t s);
 void launch_fmg_interp(int dim, bool fp32, const LevelDesc* L, const GridState* S, JobList jl,
                        int nblk, hipStream_t s);
+// plain64: level-0 solves iterate from the current x (the others from zero).
 void launch_coarse_solve(int dim, bool fp32, const LevelDesc* L, const GridState* S, JobList jl,
-                         hipStream_t s);
+                         int plain64, hipStream_t s);
 // Tail: one workgroup per job runs the V-cycle of every level from the job's level down
 // in `smem` bytes of LDS.  prepare_tail raises the kernel's dynamic-LDS limit (call once,
 // outside stream capture).  plain64: level-0 tails iterate from the current x.

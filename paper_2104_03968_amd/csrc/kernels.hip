@@ -1326,7 +1326,7 @@ __device__ __forceinline__ void block_cg(const int32_t n[3], const T* w0, const 
 
 template <int DIM, typename T>
 __global__ void __launch_bounds__(kCoarseThreads)
-k_coarse_solve(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl) {
+k_coarse_solve(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int plain64) {
     __shared__ T p_sh[kCoarseMaxLDS];
     __shared__ double red[2 * kCoarseThreads / 64];
     const LevelDesc& d = L[job_level(jl, blockIdx.x)];
@@ -1339,9 +1339,10 @@ k_coarse_solve(const LevelDesc* __restrict__ L, const GridState* __restrict__ S,
     const T* bg = Arr<T>::b(d);
     const T* ag = Arr<T>::ad(d);
     const bool has_a = ag != nullptr;
-    // The finest level of a single-level FP64 grid holds the solution itself: iterate
-    // from it.  Every other coarsest level solves for a correction from zero.
-    const bool warm = (d.level == 0) && (sizeof(T) == sizeof(double));
+    // Plain FP64 V-cycles: the finest level of a single-level grid holds the solution itself,
+    // iterate from it.  Every other coarsest level solves for a correction from zero (under CG
+    // the stored iterate is the previous correction, and nothing clears it).
+    const bool warm = plain64 && d.level == 0;
     if (ncell <= kCoarseMaxLDS) {
         block_cg<DIM, T, kCoarseThreads, kCoarseCPT>(d.n, w0, w1, w2, bg, xg, warm, p_sh, red, ag, has_a,
                                                      nb_mask(d));
@@ -4580,12 +4581,12 @@ void launch_tail(int dim, bool fp32, int bc, const LevelDesc* L, const GridState
 }
 
 void launch_coarse_solve(int dim, bool fp32, const LevelDesc* L, const GridState* S, JobList jl,
-                         hipStream_t s) {
+                         int plain64, hipStream_t s) {
     if (jl.njobs <= 0) return;
     if (acct_add(jl.cells * (fp32 ? 4.0 : 8.0) * (2 + dim))) return;   // b, faces read, x written
     FLD_DISPATCH_DIM(dim, {
-        if (fp32) hipLaunchKernelGGL((k_coarse_solve<D, float>), dim3(jl.njobs), dim3(kCoarseThreads), 0, s, L, S, jl);
-        else hipLaunchKernelGGL((k_coarse_solve<D, double>), dim3(jl.njobs), dim3(kCoarseThreads), 0, s, L, S, jl);
+        if (fp32) hipLaunchKernelGGL((k_coarse_solve<D, float>), dim3(jl.njobs), dim3(kCoarseThreads), 0, s, L, S, jl, plain64);
+        else hipLaunchKernelGGL((k_coarse_solve<D, double>), dim3(jl.njobs), dim3(kCoarseThreads), 0, s, L, S, jl, plain64);
     });
 }
 

@@ -778,7 +778,7 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
     }
     // the tail's levels are below the finest unless the whole grid lives in it
     launch_tail(dim, f32, p.nb_bc(), p.dL, p.dS, tail, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, plain64, s);
-    launch_coarse_solve(dim, f32, p.dL, p.dS, coarsest, s);
+    launch_coarse_solve(dim, f32, p.dL, p.dS, coarsest, plain64, s);
     for (int d = D.maxdepth - 1; d >= d0; --d) {
         const int nu1 = d == 0 ? p.opts.nu1 : p.nuc1, nu2 = d == 0 ? p.opts.nu2 : p.nuc2;
         if (d < L3) {
@@ -818,12 +818,10 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
 }
 
 // Whether the first smoothing kernel of level 0 in a V-cycle reads the iterate (the
-// per-colour kernels do; fused sweeps from zero and the fused 2D down pass do not).
+// per-colour kernels do; fused sweeps from zero, the fused 2D down pass, the tails and the
+// direct solve of a grid without a coarse level do not).
 static bool level0_reads_iterate(const Plan& p, const DimLists& D) {
-    // (a grid without a coarse level is solved from the stored iterate, which has to be zero)
-    if (TilePlan t; D.tile && D.smooth[0].levels.size() == D.l0_cell.levels.size() &&
-                    tile_plan(p, D, 0, p.opts.nu1, p.opts.nu2, false, t))
-        return false;
+    if (TilePlan t; D.tile && tile_plan(p, D, 0, p.opts.nu1, p.opts.nu2, false, t)) return false;
     if (D.dim == 3) return !(D.fused3 && p.sweep3 && D.levels3 >= 1);
     return !D.fused;
 }
@@ -862,7 +860,7 @@ static void enqueue_fmg(Plan& p, DimLists& D, hipStream_t s) {
     for (int d = 0; d < D.maxdepth; ++d) launch_restrict_rhs(D.dim, f32, p.dL, p.dS, D.restrict_[d].dev, p.nblk, s);
     const int plain64 = (!p.krylov && !p.mixed) ? 1 : 0;
     launch_tail(D.dim, f32, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, plain64, s);
-    launch_coarse_solve(D.dim, f32, p.dL, p.dS, D.coarsest.dev, s);
+    launch_coarse_solve(D.dim, f32, p.dL, p.dS, D.coarsest.dev, plain64, s);
     // by dimension: the 3D stages below the two finest still pay for their V-cycles
     const int fd = p.opts.fmg_depths >= 0 ? p.opts.fmg_depths : (D.dim == 3 ? 3 : 2);
     const int nv = fd > 0 ? fd : D.maxdepth;
@@ -1147,22 +1145,14 @@ void plan_coarsen(Plan& p, const DimLists& D, hipStream_t s) {
     launch_coarsen_tail(D.dim, p.mixed, p.dL, D.tail.dev, galerkin, s);
 }
 
-// Whether the V-cycle reads level 0's iterate where it starts from zero: the per-colour sweeps,
-// and the direct solve of a grid that has no other level.
-static bool iterate_read(const Plan& p, const DimLists& D) {
-    bool solved = false;
-    for (int32_t li : D.coarsest.levels) solved = solved || p.levels[li].level == 0;
-    return solved || level0_reads_iterate(p, D);
-}
-
 int plan_prologue(Plan& p, hipStream_t s, bool tensor) {
     const int zero_x = (p.krylov || p.mixed) ? 1 : 0;
     for (auto& D : p.dl) {
         if (D.l0_cell.empty()) continue;
         const JobList& l0 = D.l0_cell.dev;
         if (p.krylov && !p.any_bc && !tensor) {
-            launch_start(D.dim, p.mixed, p.dL, p.dS, l0, p.dIO, p.opts.c, p.opts.limiter, iterate_read(p, D), D.fin_fused,
-                         p.opts.rtol, p.opts.max_cycles, cell_blocks(p), s);
+            launch_start(D.dim, p.mixed, p.dL, p.dS, l0, p.dIO, p.opts.c, p.opts.limiter, level0_reads_iterate(p, D),
+                         D.fin_fused, p.opts.rtol, p.opts.max_cycles, cell_blocks(p), s);
             if (!D.fin_fused) launch_finalize(p.dL, p.dS, l0, FIN_START, p.opts.rtol, p.opts.max_cycles, s);
             plan_coarsen(p, D, s);
             continue;
