@@ -2796,6 +2796,7 @@ struct TailGeom {
     float rnx;           // 1 / nx
     int32_t ox, ob;      // (the first level has no b here)
     int32_t pm;          // neighbour mask (nb_mask): periodic axes, continuous faces
+    int32_t flat;        // cells of a colour counted along the whole level (nx odd), not row by row
 };
 
 
@@ -2803,9 +2804,23 @@ struct TailGeom {
 // lies at least 1/(2d) from an integer, far beyond the float rounding error.
 __device__ __forceinline__ int fdiv(int q, float rd) { return (int)(((float)q + 0.5f) * rd); }
 
-// Cell u of this thread among the cells of `color`: its coordinates, and whether there is one.
+// Cell m among the cells of `color`: its coordinates, and whether there is one.  Rows count
+// ceil(nx / 2) cells of a colour each; `flat` levels of odd nx take every second cell of the
+// level (of a plane, where its cells are even in number), which counts no missing ones.
 template <int DIM>
 __device__ __forceinline__ bool tail_cell(const TailGeom& g, int color, int m, int& i, int& j, int& k) {
+    if (g.flat) {
+        int c = 2 * m + color;
+        if (DIM == 3 && !(g.n[1] & 1)) {
+            const int sz = g.n[0] * g.n[1], p = m / (sz / 2);
+            c = p * sz + 2 * (m - p * (sz / 2)) + ((color + p) & 1);
+        }
+        const int r = fdiv(c, g.rnx);
+        i = c - r * g.n[0];
+        k = DIM == 3 ? fdiv(r, g.rny) : 0;
+        j = r - k * g.n[1];
+        return c < g.ncell;
+    }
     const int r = fdiv(m, g.rhx);
     j = r;
     k = 0;
@@ -3152,6 +3167,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
         t.rnx = 1.0f / (float)nown[0];
         t.rny = 1.0f / (float)nown[1];
         t.pm = pm_own;
+        t.flat = tail_half(t.n) > kTailCells / 2;
         t.ox = pad;
         t.ob = total + cells[0] + pad;
         for (int j = 0; j < mo; ++j) {

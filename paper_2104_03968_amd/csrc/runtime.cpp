@@ -293,7 +293,9 @@ static size_t tail_bytes(const Plan& p, int g, int t) {
 
 // Whether grid g's levels from t down fit the tail: the first level's colours in the
 // workgroup's registers, the second's too or in a wavefront's, those below in a wavefront's
-// each; the coarsest (which may be the second) of at most kTailMaxCoarsest cells.
+// each; the coarsest (which may be the second) of at most kTailMaxCoarsest cells.  (A level of
+// odd nx counts rows of ceil(nx / 2) cells; a single one of up to kTailMaxCoarsest cells whose
+// rows don't fit is counted flat.)
 static bool tail_fits(const Plan& p, int g, int t) {
     const LevelDesc* const d = &p.levels[p.level0[g]];
     const int L = p.nlev[g];
@@ -302,6 +304,7 @@ static bool tail_fits(const Plan& p, int g, int t) {
         const int64_t row = (int64_t)(d[l].n[0] + 1) / 2 * d[l].n[1];
         const int64_t half = row * d[l].n[2];
         const bool whole = l == t || (l == t + 1 && l == L - 1);   // on the workgroup, two cells a thread
+        if (t == L - 1 && (int64_t)d[l].n[0] * d[l].n[1] * d[l].n[2] <= kTailMaxCoarsest) continue;
         if (half > (whole ? kTailCells / 2 : (l == t + 1 && p.grids[g].ndim == 2 ? kTailThreads : kTailWaveHalf))) return false;
     }
     return true;
@@ -343,10 +346,10 @@ static void build_lists(Plan& p) {
             if (p.tail_lev[g] >= 0) {
                 D.tail.levels.push_back(l0 + p.tail_lev[g]);
                 D.tail_smem = std::max(D.tail_smem, tail_bytes(p, g, p.tail_lev[g]));
-                // (a level of one colour's cells a row longer than the other's: rows of ceil(nx / 2))
+                // (rows of ceil(nx / 2) cells of a colour, or counted flat)
                 const LevelDesc& f = p.levels[l0 + p.tail_lev[g]];
-                const int64_t half = (int64_t)((f.n[0] + 1) / 2) * f.n[1] * f.n[2];
-                D.tail_cpc = std::max(D.tail_cpc, (int)((half + kTailThreads - 1) / kTailThreads));
+                const int half = std::min(tail_half(f.n), kTailCells / 2);
+                D.tail_cpc = std::max(D.tail_cpc, (half + kTailThreads - 1) / kTailThreads);
             } else {
                 D.coarsest.levels.push_back(l0 + p.nlev[g] - 1);
             }
