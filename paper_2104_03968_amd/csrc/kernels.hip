@@ -3088,21 +3088,22 @@ __device__ __forceinline__ void tail_cg(const TailCells<DIM, T, BC, CPC>& c, con
     c.template half<NT>(x, g, 0);
 }
 
-// The coarsest level's solve by the whole workgroup, from x.
+// The coarsest level's solve by the whole workgroup, from x.  op: its operator where it does not
+// split (faces, then the Dirichlet couplings).
 template <int DIM, typename T, bool BC>
-__device__ __forceinline__ void tail_coarsest(const TailGeom& g, const LevelDesc& d, const T* bs, bool has_a, bool split,
-                                              T* x, T* y, int spare, double* sh) {
+__device__ __forceinline__ void tail_coarsest(const TailGeom& g, const LevelDesc& d, const T* bs, const T* op, bool has_a,
+                                              bool split, T* x, T* y, int spare, double* sh) {
     constexpr int NT = kTailThreads, CPC = kTailMaxCoarsest / 2 / NT;
     if constexpr (BC) {
         if (!split && g.ncell <= 64) {                         // a wavefront needs no barriers
             if (threadIdx.x < 64)
-                block_cg<DIM, T, 64, 1>(g.n, Arr<T>::w(d, 0), Arr<T>::w(d, 1), DIM == 3 ? Arr<T>::w(d, 2) : nullptr, bs,
-                                        x, true, y, sh, Arr<T>::ad(d), has_a, g.pm);
+                block_cg<DIM, T, 64, 1>(g.n, op, op + g.ncell, op + 2 * g.ncell, bs, x, true, y, sh, op + DIM * g.ncell,
+                                        has_a, g.pm);
             return;
         }
         if (!split) {
-            block_cg<DIM, T, NT, 2 * CPC>(g.n, Arr<T>::w(d, 0), Arr<T>::w(d, 1), DIM == 3 ? Arr<T>::w(d, 2) : nullptr, bs,
-                                          x, true, y, sh, Arr<T>::ad(d), has_a, g.pm);
+            block_cg<DIM, T, NT, 2 * CPC>(g.n, op, op + g.ncell, op + 2 * g.ncell, bs, x, true, y, sh,
+                                          op + DIM * g.ncell, has_a, g.pm);
             return;
         }
     }
@@ -3113,15 +3114,15 @@ __device__ __forceinline__ void tail_coarsest(const TailGeom& g, const LevelDesc
 }
 
 // The same as a call, for a coarsest level below others (their operators stay in the caller's
-// registers; inlined, its own would make them spill on every path): oy, spare and the level's
-// arrays as offsets in the tail's LDS.
+// registers; inlined, its own would make them spill on every path): oy, oop, spare and the
+// level's arrays as offsets in the tail's LDS.
 template <int DIM, typename T, bool BC>
-__device__ __attribute__((noinline)) void tail_coarsest_below(const TailGeom* gp, const LevelDesc* d, int oy, int spare,
-                                                              bool has_a, bool split, double* sh) {
+__device__ __attribute__((noinline)) void tail_coarsest_below(const TailGeom* gp, const LevelDesc* d, int oy, int oop,
+                                                              int spare, bool has_a, bool split, double* sh) {
     extern __shared__ __align__(16) unsigned char tail_smem[];
     T* const base = reinterpret_cast<T*>(tail_smem);
     const TailGeom g = *gp;
-    tail_coarsest<DIM, T, BC>(g, *d, base + g.ob, has_a, split, base + g.ox, base + oy, spare - g.ox, sh);
+    tail_coarsest<DIM, T, BC>(g, *d, base + g.ob, base + oop, has_a, split, base + g.ox, base + oy, spare - g.ox, sh);
 }
 
 // BC: the plan has Dirichlet or periodic faces (extra diagonal, wrapped neighbours).  CPC: the
@@ -3154,7 +3155,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
     if (!act) return;                                          // uniform
     __syncthreads();
     // LDS: a pad, every level's iterate, a pad; the first level's residuals (also the coarsest
-    // solve's vector) and a pad; every level's b
+    // solve's vector) and a pad; every level's b; the coarsest operator where it is no colour's solve
     const int pad = tail_pad(d0.n);
     int total = 2 * pad;
     for (int j = 0; j < nl; ++j) total += cells[j];
@@ -3193,6 +3194,18 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
         split = (gl.pm >> 3) == 0;
         for (int a = 0; a < DIM; ++a) split = split && !(((gl.pm >> a) & 1) && (gl.n[a] & 1));
     }
+    // else its operator past every level's b: each iteration on all cells reads it (from global
+    // memory, a step of 100 x 180 cells with periodic x and a 25 x 45 coarsest level took 925 us
+    // in place of 853, one of 45 x 45 with continuous faces 660 in place of 328)
+    const int oop = gl.ob + gl.ncell;
+    if (BC && !split) {
+        const LevelDesc& d = L[first + nl - 1];
+        const int na = DIM + (has_a ? 1 : 0);
+        for (int a = 0; a < na; ++a) {
+            const gptr<T> src = as_global(a < DIM ? Arr<T>::w(d, a) : Arr<T>::ad(d));
+            for (int c = threadIdx.x; c < gl.ncell; c += NT) base[oop + a * gl.ncell + c] = src[c];
+        }
+    }
     if (nl == 1) {
         // the only level: at most kTailMaxCoarsest cells, solved from the stored x (warm) or zero
         const gptr<T> gb = as_global(Arr<T>::b(d0));
@@ -3201,7 +3214,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
             if (warm) x0[c] = gx[c];
         }
         __syncthreads();
-        tail_coarsest<DIM, T, BC>(g0, d0, base + g0.ob, has_a, split, x0, y, spare - g0.ox, sh);
+        tail_coarsest<DIM, T, BC>(g0, d0, base + g0.ob, base + oop, has_a, split, x0, y, spare - g0.ox, sh);
         __syncthreads();
         for (int c = threadIdx.x; c < g0.ncell; c += NT) gx[c] = x0[c];
         return;
@@ -3244,7 +3257,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
             tail_cg<DIM, T, BC, 64, CPW>(cw, gm, has_a, base + gm.ox, y, sh);
         }
     } else {
-        tail_coarsest_below<DIM, T, BC>(&tl[nl - 1], &L[first + nl - 1], total, spare, has_a, split, sh);
+        tail_coarsest_below<DIM, T, BC>(&tl[nl - 1], &L[first + nl - 1], total, oop, spare, has_a, split, sh);
     }
     __syncthreads();
     for (int m = nl - 2; m >= mw; --m) {

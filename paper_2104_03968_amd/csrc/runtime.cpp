@@ -282,12 +282,23 @@ static void build_levels(Plan& p) {
     }
 }
 
+// Whether grid g's coarsest level splits red-black with a symmetric operator (the tail solves it
+// on one colour): no periodic axis of an odd length, no continuous face (of level 0 alone).
+static bool coarsest_splits(const Plan& p, int g) {
+    const LevelDesc& d = p.levels[p.level0[g] + p.nlev[g] - 1];
+    for (int a = 0; a < d.ndim; ++a)
+        if (((d.per_mask >> a) & 1) && (d.n[a] & 1)) return false;
+    return d.cont_mask == 0;
+}
+
 // LDS bytes of grid g's tail from level t: every level's iterate and right-hand side, the first
-// level's residuals, three pads.
+// level's residuals, three pads; the coarsest operator where it is solved on all cells.
 static size_t tail_bytes(const Plan& p, int g, int t) {
     const LevelDesc* const d = &p.levels[p.level0[g]];
     size_t cells = 3 * (size_t)tail_pad(d[t].n) + (size_t)d[t].n[0] * d[t].n[1] * d[t].n[2];
     for (int l = t; l < p.nlev[g]; ++l) cells += 2 * (size_t)d[l].n[0] * d[l].n[1] * d[l].n[2];
+    const LevelDesc& c = d[p.nlev[g] - 1];
+    if (!coarsest_splits(p, g)) cells += (size_t)(c.ndim + (p.has_dir ? 1 : 0)) * c.n[0] * c.n[1] * c.n[2];
     return cells * (p.mixed ? 4 : 8);
 }
 

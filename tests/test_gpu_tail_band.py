@@ -47,7 +47,8 @@ def test_band_is_the_tails_and_meets_the_oracle(shape, precision):
 
 @pytest.mark.parametrize("shape", [(45, 45), (12, 13, 13), (13, 12, 13), (22, 93)])
 def test_band_with_held_and_wrapped_faces(shape):
-    # held faces split red-black with the flat count; odd periodic axes are solved on all cells
+    # held faces split red-black with the flat count; odd periodic axes are solved on all cells,
+    # with the operator in LDS
     g = W.random_grid(shape, 97000 + sum(shape), dt=5e-3)
     P, D = "periodic", "dirichlet"
     code = {P: fld.FLD_BC_PERIODIC, D: fld.FLD_BC_DIRICHLET}
