@@ -26,7 +26,8 @@ constexpr int kCoarseCPT = 4;
 constexpr int kCoarseMaxLDS = kCoarseThreads * kCoarseCPT;   // 4096 cells
 // LDS tail: one 512-thread workgroup per grid (measured ahead of 256 and 1024), its first
 // and its coarsest level of at most 4 cells a thread (8, a 64^2 level: 48 us a call for 1024^2,
-// against 17 us and two launches of 5.5 us without that level).
+// against 17 us and two launches of 5.5 us without that level).  A lead level of more cells, held
+// in LDS, heads the tails of the grids that choose_tails names.
 constexpr int kTailThreads = 512;
 constexpr int kTailCells = 4 * kTailThreads;                 // 2048 cells: 32^2, 12^3
 constexpr int kTailMaxCoarsest = 4 * kTailThreads;           // 2048 cells
@@ -399,8 +400,9 @@ void launch_tile(int dim, bool fp32, int bc, const LevelDesc* L, const GridState
                  int prolong, int restr, int c0, int from_xs, hipStream_t s);
 // bc: the plan has Dirichlet or periodic faces.
 void launch_tail(int dim, bool fp32, int bc, const LevelDesc* L, const GridState* S, JobList jl, size_t smem,
-                 int cpc, int nu1, int nu2, int plain64, hipStream_t s);
-// cpc: cells of one colour of the first level a thread holds (1 or 2).
+                 int cpc, int lead, int nu1, int nu2, int plain64, hipStream_t s);
+// cpc: cells of one colour of the first level a thread holds (1 or 2).  lead: levels of more than
+// kTailCells cells head the tail of some grids.
 constexpr size_t kTailLdsBudget = 150 * 1024;
 // select: 0 = active grids, 1 = inactive grids whose status is FLD_OK (convergence check),
 // 2 = active grids at iteration 0 (sent back to iterate by a check).

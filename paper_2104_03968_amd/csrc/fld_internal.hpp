@@ -68,6 +68,7 @@ struct DimLists {
     std::vector<HostList> tail_from, coarsest_from;
     size_t tail_smem = 0;                      // LDS bytes of the largest tail
     int tail_cpc = 1;                          // cells of one colour a thread of its first level
+    int tail_lead = 0;                         // some tails are headed by a level of more than kTailCells cells
     bool fin_fused = false;                    // finish reductions in the last block (small grids)
     bool fold = false;                         // CG scalars formed in the consuming kernels (mid-sized grids)
     HostList pq3;                              // level 0, marching CG tiles (zero-flux operators): z-march

@@ -2769,9 +2769,9 @@ k_tile(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
 
 // ---------------------------------------------------------------------------
 // Tail: one workgroup per grid runs the whole V-cycle below a level T (of at most
-// kTailCells cells), so the coarse levels cost one launch instead of a few per level.  The
-// restriction from level T-1 left b_T in global memory and the prolongation to level T-1
-// reads the correction x_T back from global memory.
+// kTailCells cells, or a lead level of more), so the coarse levels cost one launch instead
+// of a few per level.  The restriction from level T-1 left b_T in global memory and the
+// prolongation to level T-1 reads the correction x_T back from global memory.
 //
 // What bounds it is one workgroup's chain of phases (12 half sweeps a level), so a phase is
 // kept short: each thread owns the same cells of a level for all its sweeps and keeps their
@@ -3125,9 +3125,111 @@ __device__ __attribute__((noinline)) void tail_coarsest_below(const TailGeom* gp
     tail_coarsest<DIM, T, BC>(g, *d, base + g.ob, base + oop, has_a, split, base + g.ox, base + oy, spare - g.ox, sh);
 }
 
+// Lead level: one of more than kTailCells cells above the tail's first level (choose_tails says
+// where).  The registers do not hold its operator (two more cells of a colour a thread spill), so
+// iterate, right-hand side and operator sit in LDS from `o` on and are read again on every visit
+// of a cell.
+template <int DIM, typename T, bool BC>
+struct TailLead {
+    static constexpr int NT = kTailThreads;
+    TailGeom g;
+    bool has_a;
+    T *x, *b, *w[3], *a;
+
+    __device__ __forceinline__ TailLead(const LevelDesc& d, bool has_a_, T* o) : has_a(has_a_) {
+        for (int q = 0; q < 3; ++q) g.n[q] = d.n[q];
+        g.ncell = d.n[0] * d.n[1] * d.n[2];
+        g.hx = d.n[0] / 2;                                     // even: the level has a coarser one
+        g.rhx = 1.0f / (float)g.hx;
+        g.rnx = 1.0f / (float)d.n[0];
+        g.rny = 1.0f / (float)d.n[1];
+        g.pm = BC ? nb_mask(d) : 0;
+        g.flat = 0;
+        x = o;
+        b = o + g.ncell;
+        for (int q = 0; q < 3; ++q) w[q] = o + (2 + q) * g.ncell;   // (unused past DIM)
+        a = o + (2 + DIM) * g.ncell;                           // unused without Dirichlet faces
+    }
+    __device__ __forceinline__ void load(const LevelDesc& d, bool warm) const {
+        const gptr<T> xs = as_global(Arr<T>::x(d)), bs = as_global(Arr<T>::b(d));
+        const gptr<T> w0 = as_global(Arr<T>::w(d, 0)), w1 = as_global(Arr<T>::w(d, 1));
+        const gptr<T> w2 = as_global(DIM == 3 ? Arr<T>::w(d, 2) : Arr<T>::w(d, 0));
+        const gptr<T> as = as_global(has_a ? Arr<T>::ad(d) : Arr<T>::w(d, 0));
+        for (int c = threadIdx.x; c < g.ncell; c += NT) {
+            const T xv = warm ? xs[c] : T(0), bv = bs[c], v0 = w0[c], v1 = w1[c], v2 = w2[c], av = as[c];
+            x[c] = xv;
+            b[c] = bv;
+            w[0][c] = v0;
+            w[1][c] = v1;
+            if (DIM == 3) w[2][c] = v2;
+            if (BC && has_a) a[c] = av;
+        }
+        __syncthreads();
+    }
+    __device__ __forceinline__ void half(int color) const {
+        const int sy = g.n[0], sz = g.n[0] * g.n[1];
+        for (int m = threadIdx.x; m < g.ncell / 2; m += NT) {
+            int i, j, k;
+            tail_cell<DIM>(g, color, m, i, j, k);
+            const int c = i + j * sy + k * sz;
+            T s = b[c], dg = T(1), wn, xn;
+            nb_lo(w[0], x, c, i, g.n[0], 1, g.pm, 0, wn, xn);
+            s += wn * xn; dg += wn;
+            nb_hi(w[0], x, c, i, g.n[0], 1, g.pm, 0, wn, xn);
+            s += wn * xn; dg += wn;
+            nb_lo(w[1], x, c, j, g.n[1], sy, g.pm, 1, wn, xn);
+            s += wn * xn; dg += wn;
+            nb_hi(w[1], x, c, j, g.n[1], sy, g.pm, 1, wn, xn);
+            s += wn * xn; dg += wn;
+            if (DIM == 3) {
+                nb_lo(w[2], x, c, k, g.n[2], sz, g.pm, 2, wn, xn);
+                s += wn * xn; dg += wn;
+                nb_hi(w[2], x, c, k, g.n[2], sz, g.pm, 2, wn, xn);
+                s += wn * xn; dg += wn;
+            }
+            if (BC && has_a) dg += a[c];
+            x[c] = s / dg;
+        }
+        __syncthreads();
+    }
+    // nu sweeps, then the residual averaged onto the coarse level's right-hand side
+    __device__ __forceinline__ void down(const TailGeom& cg, T* cb, int nu) const {
+        for (int it = 0; it < nu; ++it) {
+            half(0);
+            half(1);
+        }
+        for (int c = threadIdx.x; c < cg.ncell; c += NT) {
+            const int r = fdiv(c, cg.rnx), I = c - r * cg.n[0];
+            const int K = DIM == 3 ? fdiv(r, cg.rny) : 0, J = r - K * cg.n[1];
+            T sum = T(0);
+#pragma unroll
+            for (int q = 0; q < (1 << DIM); ++q)
+                sum += residual_at<DIM, T>(x, b, w[0], w[1], w[2], g.n, 2 * I + (q & 1), 2 * J + ((q >> 1) & 1),
+                                           DIM == 3 ? 2 * K + (q >> 2) : 0, a, BC && has_a, g.pm);
+            cb[c] = sum * T(DIM == 3 ? 0.125 : 0.25);
+        }
+        __syncthreads();
+    }
+    // add the coarse correction, then nu sweeps; the iterate goes to global memory
+    __device__ __forceinline__ void up(const TailGeom& cg, const T* cx, int nu, gptr<T> out) const {
+        for (int c = threadIdx.x; c < g.ncell; c += NT) {
+            const int r = fdiv(c, g.rnx), i = c - r * g.n[0];
+            const int k = DIM == 3 ? fdiv(r, g.rny) : 0, j = r - k * g.n[1];
+            x[c] += cx[(i >> 1) + cg.n[0] * ((j >> 1) + cg.n[1] * (k >> 1))];
+        }
+        __syncthreads();
+        for (int it = 0; it < nu; ++it) {
+            half(1);
+            half(0);
+        }
+        for (int c = threadIdx.x; c < g.ncell; c += NT) out[c] = x[c];
+    }
+};
+
 // BC: the plan has Dirichlet or periodic faces (extra diagonal, wrapped neighbours).  CPC: the
-// cells of one colour of the first level a thread holds.
-template <int DIM, typename T, bool BC, int CPC>
+// cells of one colour of the first level a thread holds.  LEAD: levels of more than kTailCells
+// cells head the tail of some jobs.
+template <int DIM, typename T, bool BC, int CPC, bool LEAD>
 __global__ void __launch_bounds__(kTailThreads)
 k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int nu1, int nu2,
        int plain64) {
@@ -3136,7 +3238,10 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
     __shared__ int32_t cells[kMaxTail];
     __shared__ double sh[3 * kTailThreads / 64];
     constexpr int NT = kTailThreads, CPW = kTailWaveHalf / 64;
-    const int first = job_level(jl, blockIdx.x);
+    const int top = job_level(jl, blockIdx.x);
+    const LevelDesc& dt = L[top];
+    const bool lead = LEAD && dt.n[0] * dt.n[1] * dt.n[2] > kTailCells;   // uniform
+    const int first = lead ? top + 1 : top;
     const LevelDesc& d0 = L[first];
     const int act = S[d0.sidx].active;
     const bool has_a = BC && Arr<T>::ad(d0) != nullptr;
@@ -3155,7 +3260,8 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
     if (!act) return;                                          // uniform
     __syncthreads();
     // LDS: a pad, every level's iterate, a pad; the first level's residuals (also the coarsest
-    // solve's vector) and a pad; every level's b; the coarsest operator where it is no colour's solve
+    // solve's vector) and a pad; every level's b; the coarsest operator where it is no colour's
+    // solve; the lead level's arrays
     const int pad = tail_pad(d0.n);
     int total = 2 * pad;
     for (int j = 0; j < nl; ++j) total += cells[j];
@@ -3206,15 +3312,27 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
             for (int c = threadIdx.x; c < gl.ncell; c += NT) base[oop + a * gl.ncell + c] = src[c];
         }
     }
+    T* const lead_at = base + oop + (split ? 0 : (DIM + (has_a ? 1 : 0)) * gl.ncell);
+    auto lead_up = [&] {
+        // (its arrays are still in LDS: the struct alone is formed again)
+        __syncthreads();
+        TailLead<DIM, T, BC>(dt, has_a, lead_at).up(g0, x0, nu2, as_global(Arr<T>::x(dt)));
+    };
+    if (lead) {
+        TailLead<DIM, T, BC> ld(dt, has_a, lead_at);
+        ld.load(dt, plain64 && dt.level == 0);
+        ld.down(g0, base + g0.ob, nu1);
+    }
     if (nl == 1) {
         // the only level: at most kTailMaxCoarsest cells, solved from the stored x (warm) or zero
         const gptr<T> gb = as_global(Arr<T>::b(d0));
-        for (int c = threadIdx.x; c < g0.ncell; c += NT) {
+        for (int c = threadIdx.x; c < g0.ncell && !lead; c += NT) {
             base[g0.ob + c] = gb[c];
             if (warm) x0[c] = gx[c];
         }
         __syncthreads();
         tail_coarsest<DIM, T, BC>(g0, d0, base + g0.ob, base + oop, has_a, split, x0, y, spare - g0.ox, sh);
+        if (lead) return lead_up();
         __syncthreads();
         for (int c = threadIdx.x; c < g0.ncell; c += NT) gx[c] = x0[c];
         return;
@@ -3229,7 +3347,8 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
     TailCells<DIM, T, BC, CPC> c0;
     TailCells<DIM, T, BC, 1> c1;
     TailCells<DIM, T, BC, CPW> cw;
-    c0.template load<NT>(g0, d0, has_a, spare - g0.ox, threadIdx.x, true);
+    c0.template load<NT>(g0, d0, has_a, spare - g0.ox, threadIdx.x, !lead);
+    if (lead) c0.set_b(g0, base + g0.ob);
     if (DIM == 2 && wide1 && nl > 2) c1.template load<NT>(g1, L[first + 1], has_a, spare - g1.ox, threadIdx.x, false);
     const int mw = wide1 ? 2 : 1;                              // first level of a wavefront's own
     const bool mine = wave >= mw && wave < nl;
@@ -3269,6 +3388,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
         c1.template up<NT>(base + g1.ox, g1, g2, base + g2.ox, nu2, threadIdx.x);
     }
     c0.template up<NT>(x0, g0, g1, base + g1.ox, nu2, threadIdx.x);
+    if (lead) return lead_up();
     for (int c = threadIdx.x; c < g0.ncell; c += NT) gx[c] = x0[c];
 }
 
@@ -4575,7 +4695,8 @@ void launch_tile(int dim, bool fp32, int bc, const LevelDesc* L, const GridState
 
 template <int DIM, typename T, bool BC>
 static hipError_t tail_lds(size_t smem) {
-    for (const void* k : {(const void*)k_tail<DIM, T, BC, 1>, (const void*)k_tail<DIM, T, BC, 2>}) {
+    for (const void* k : {(const void*)k_tail<DIM, T, BC, 1, false>, (const void*)k_tail<DIM, T, BC, 2, false>,
+                          (const void*)k_tail<DIM, T, BC, 2, true>}) {
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
     }
@@ -4594,13 +4715,13 @@ int prepare_tail(int dim, bool fp32, size_t smem) {
 }
 
 void launch_tail(int dim, bool fp32, int bc, const LevelDesc* L, const GridState* S, JobList jl, size_t smem,
-                 int cpc, int nu1, int nu2, int plain64, hipStream_t s) {
+                 int cpc, int lead, int nu1, int nu2, int plain64, hipStream_t s) {
     if (jl.njobs <= 0) return;
     // list: each grid's first tail level; its b and the face arrays of every tail level
     // (2^d / (2^d - 1) times the first level's) read once, its x written
     if (acct_add(jl.cells * (fp32 ? 4.0 : 8.0) * (2.0 + dim * (double)(1 << dim) / ((1 << dim) - 1)))) return;
-#define FLD_TAIL(T_, B, C) hipLaunchKernelGGL((k_tail<D, T_, B, C>), dim3(jl.njobs), dim3(kTailThreads), smem, s, L, S, jl, nu1, nu2, plain64)
-#define FLD_TAIL_CPC(T_, B) do { if (cpc <= 1) FLD_TAIL(T_, B, 1); else FLD_TAIL(T_, B, 2); } while (0)
+#define FLD_TAIL(T_, B, C, H) hipLaunchKernelGGL((k_tail<D, T_, B, C, H>), dim3(jl.njobs), dim3(kTailThreads), smem, s, L, S, jl, nu1, nu2, plain64)
+#define FLD_TAIL_CPC(T_, B) do { if (lead) FLD_TAIL(T_, B, 2, true); else if (cpc <= 1) FLD_TAIL(T_, B, 1, false); else FLD_TAIL(T_, B, 2, false); } while (0)
     FLD_DISPATCH_DIM(dim, {
         if (bc) { if (fp32) FLD_TAIL_CPC(float, true); else FLD_TAIL_CPC(double, true); }
         else { if (fp32) FLD_TAIL_CPC(float, false); else FLD_TAIL_CPC(double, false); }

@@ -291,6 +291,21 @@ static bool coarsest_splits(const Plan& p, int g) {
     return d.cont_mask == 0;
 }
 
+// What the levels above the tail can run (and do with fld_opts.fused) other than a launch per
+// colour: in 2D the fused passes, in 3D the fused sweeps, which know no Dirichlet couplings or
+// wrapped neighbours and alternate between x and xs, so that a V-cycle's sweep count has to be
+// even for its result to end in x; the small-level passes where the operator differs from zero
+// flux (conjugate gradients only: their second iterate on level 0 is the CG product vector).
+static bool fuses2(const Plan& p) {
+    return !p.nb_bc() && fused2_supported(p.opts.nu1) && fused2_supported(p.opts.nu2) && fused2_supported(p.nuc1) &&
+           fused2_supported(p.nuc2);
+}
+static bool fuses3(const Plan& p) {
+    return !p.nb_bc() && fused3_supported(p.mixed) && p.opts.nu1 >= 1 && p.opts.nu2 >= 1 &&
+           (p.opts.nu1 + p.opts.nu2) % 2 == 0 && p.nuc1 >= 1 && p.nuc2 >= 1 && (p.nuc1 + p.nuc2) % 2 == 0;
+}
+static bool tiles_bc(const Plan& p) { return p.nb_bc() && p.krylov; }
+
 // LDS bytes of grid g's tail from level t: every level's iterate and right-hand side, the first
 // level's residuals, three pads; the coarsest operator where it is solved on all cells.
 static size_t tail_bytes(const Plan& p, int g, int t) {
@@ -321,12 +336,36 @@ static bool tail_fits(const Plan& p, int g, int t) {
     return true;
 }
 
-// First level of each grid's LDS tail: the finest from which its levels fit.
+// LDS bytes of grid g's level t - 1 ahead of its tail from level t: iterate, right-hand side,
+// operator.
+static size_t lead_bytes(const Plan& p, int g, int t) {
+    const LevelDesc& d = p.levels[p.level0[g] + t - 1];
+    return (size_t)(2 + d.ndim + (p.has_dir ? 1 : 0)) * d.n[0] * d.n[1] * d.n[2] * (p.mixed ? 4 : 8);
+}
+
+// First level of each grid's LDS tail: the finest from which its levels fit, or the level above
+// that where it fits the LDS too, as a lead level, and pays:
+//  * where the levels above the tail can only sweep per colour, so that the lead level's launches
+//    cost more than its sweeps on one compute unit (64^2 in FP32 with continuous faces: 669 us
+//    without it, 536 us with; 128 such grids: 1406 and 807 us);
+//  * whole 3D grids (14^3 in FP64: 232 and 172 us; 128 of them: 1046 and 730 us);
+//  * whole 2D grids of up to 2 kTailCells cells in FP32 with zero-flux faces (64^2: 337 and 325 us;
+//    512 of them: 3099 and 2744 us; but 72^2: 293 and 351 us).
+// Not others: 60^2 in FP64 274 and 328 us, 32^3 in FP32 361 and 411 us.  fld_opts.fused has no say:
+// its choices give the same bits, and a tail sweeps level 0 as often as the coarse levels.
 static void choose_tails(Plan& p) {
     p.tail_lev.assign(p.ngrids(), -1);
     for (int g = 0; g < p.ngrids(); ++g) {
-        for (int t = 0; t < p.nlev[g] && p.tail_lev[g] < 0; ++t)
-            if (tail_fits(p, g, t)) p.tail_lev[g] = t;
+        int& t = p.tail_lev[g];
+        for (int l = 0; l < p.nlev[g] && t < 0; ++l)
+            if (tail_fits(p, g, l)) t = l;
+        if (t < 1 || tail_bytes(p, g, t) + lead_bytes(p, g, t) > kTailLdsBudget) continue;
+        const LevelDesc& f = p.levels[p.level0[g] + t - 1];
+        const int64_t n = (int64_t)f.n[0] * f.n[1] * f.n[2];
+        if (n <= kTailCells) continue;                         // (the tail knows a lead level by its size)
+        const bool per_colour = !(f.ndim == 2 ? fuses2(p) : fuses3(p)) && !tiles_bc(p);
+        const bool whole = t == 1 && (f.ndim == 3 || (p.mixed && !p.nb_bc() && n <= 2 * kTailCells));
+        if (per_colour || whole) --t;
     }
 }
 
@@ -356,9 +395,12 @@ static void build_lists(Plan& p) {
             }
             if (p.tail_lev[g] >= 0) {
                 D.tail.levels.push_back(l0 + p.tail_lev[g]);
-                D.tail_smem = std::max(D.tail_smem, tail_bytes(p, g, p.tail_lev[g]));
-                // (rows of ceil(nx / 2) cells of a colour, or counted flat)
                 const LevelDesc& f = p.levels[l0 + p.tail_lev[g]];
+                const bool lead = (int64_t)f.n[0] * f.n[1] * f.n[2] > kTailCells;
+                const int t = p.tail_lev[g] + (lead ? 1 : 0);
+                D.tail_lead |= lead;
+                D.tail_smem = std::max(D.tail_smem, tail_bytes(p, g, t) + (lead ? lead_bytes(p, g, t) : 0));
+                // (rows of ceil(nx / 2) cells of a colour, or counted flat)
                 const int half = std::min(tail_half(f.n), kTailCells / 2);
                 D.tail_cpc = std::max(D.tail_cpc, (half + kTailThreads - 1) / kTailThreads);
             } else {
@@ -418,10 +460,7 @@ static void build_lists(Plan& p) {
             D.pq3.prefix.assign(1, 0);
             for (int32_t li : D.pq3.levels) D.pq3.prefix.push_back(D.pq3.prefix.back() + pq3_tiles(p.levels[li].n, D.fz_pq));
         }
-        // the fused level kernels know no Dirichlet couplings or wrapped neighbours: such plans
-        // sweep per colour
-        D.fused = D.dim == 2 && p.opts.fused && !p.nb_bc() && fused2_supported(p.opts.nu1) &&
-                  fused2_supported(p.opts.nu2) && fused2_supported(p.nuc1) && fused2_supported(p.nuc2);
+        D.fused = D.dim == 2 && p.opts.fused && fuses2(p);
         D.down2.resize(D.fused ? maxdepth : 0);
         D.up2.resize(D.fused ? maxdepth : 0);
         D.mdn.resize(D.fused ? maxdepth : 0);
@@ -459,12 +498,7 @@ static void build_lists(Plan& p) {
             for (int32_t li : mu.levels)
                 mu.prefix.push_back(mu.prefix.back() + march_tiles(p.levels[li].n, n2, false, D.mfz[dpt]));
         }
-        // fused 3D sweeps alternate between x and xs, so the V-cycle's sweep count must be
-        // even for its result to end in x
-        D.fused3 = D.dim == 3 && p.opts.fused && !p.nb_bc() && fused3_supported(p.mixed) &&
-                   p.opts.nu1 >= 1 &&
-                   p.opts.nu2 >= 1 && (p.opts.nu1 + p.opts.nu2) % 2 == 0 && p.nuc1 >= 1 && p.nuc2 >= 1 &&
-                   (p.nuc1 + p.nuc2) % 2 == 0;
+        D.fused3 = D.dim == 3 && p.opts.fused && fuses3(p);
         D.sw3.resize(D.fused3 ? maxdepth : 0);
         D.sr3.resize(D.fused3 ? maxdepth : 0);
         D.m3.resize(D.fused3 ? maxdepth : 0);
@@ -477,9 +511,8 @@ static void build_lists(Plan& p) {
         finish_fused(p, D);
         // The small-level passes take the depths that no other fused pass does: in 3D those
         // past the sweeps' leading depths, and every depth of a plan whose operator differs
-        // from zero flux (conjugate gradients only: their second iterate on level 0 is the
-        // CG product vector).  They alternate between x and xs.
-        D.tile = maxdepth > 0 && ((D.dim == 3 && D.fused3) || (p.nb_bc() && p.krylov && p.opts.fused));
+        // from zero flux.  They alternate between x and xs.
+        D.tile = maxdepth > 0 && ((D.dim == 3 && D.fused3) || (tiles_bc(p) && p.opts.fused));
         for (int ns = 1; ns <= kTileMaxNs; ++ns) {
             D.tl[ns - 1].assign(D.tile ? maxdepth : 0, HostList{});
             for (int dpt = 0; dpt < (int)D.tl[ns - 1].size(); ++dpt) {
@@ -791,7 +824,7 @@ static void enqueue_mg_from(Plan& p, DimLists& D, hipStream_t s, int d0, int loa
         launch_restrict(dim, f32, p.dL, p.dS, D.restrict_[d].dev, p.nblk, s);
     }
     // the tail's levels are below the finest unless the whole grid lives in it
-    launch_tail(dim, f32, p.nb_bc(), p.dL, p.dS, tail, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, plain64, s);
+    launch_tail(dim, f32, p.nb_bc(), p.dL, p.dS, tail, D.tail_smem, D.tail_cpc, D.tail_lead, p.nuc1, p.nuc2, plain64, s);
     launch_coarse_solve(dim, f32, p.dL, p.dS, coarsest, plain64, s);
     for (int d = D.maxdepth - 1; d >= d0; --d) {
         const int nu1 = d == 0 ? p.opts.nu1 : p.nuc1, nu2 = d == 0 ? p.opts.nu2 : p.nuc2;
@@ -873,7 +906,7 @@ static void enqueue_fmg(Plan& p, DimLists& D, hipStream_t s) {
     const bool f32 = p.mixed;
     for (int d = 0; d < D.maxdepth; ++d) launch_restrict_rhs(D.dim, f32, p.dL, p.dS, D.restrict_[d].dev, p.nblk, s);
     const int plain64 = (!p.krylov && !p.mixed) ? 1 : 0;
-    launch_tail(D.dim, f32, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, plain64, s);
+    launch_tail(D.dim, f32, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, D.tail_lead, p.nuc1, p.nuc2, plain64, s);
     launch_coarse_solve(D.dim, f32, p.dL, p.dS, D.coarsest.dev, plain64, s);
     // by dimension: the 3D stages below the two finest still pay for their V-cycles
     const int fd = p.opts.fmg_depths >= 0 ? p.opts.fmg_depths : (D.dim == 3 ? 3 : 2);
@@ -1623,7 +1656,7 @@ static int profile_kernel(Plan& p, int kernel, int level, int reps, hipStream_t 
                         launch_sweep3(p.mixed, p.dL, p.dS, D.sw3[level].dev, 0, 0, 0, D.fz_s[level], p.nblk, s);
                     break;
                 case FLD_KERNEL_TAIL:
-                    launch_tail(D.dim, p.mixed, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, p.nuc1, p.nuc2, 0, s);
+                    launch_tail(D.dim, p.mixed, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, D.tail_lead, p.nuc1, p.nuc2, 0, s);
                     break;
                 default: break;
             }
