@@ -133,6 +133,25 @@ inline int cell_blocks(const Plan&) { return 1 << 30; }
 // compute unit (fld_opts.fused = 1).
 constexpr int kMarchMinBlocks = 4;
 
+// The launches of a depth's marching sweeps: two sweeps from zero first on the way down, two
+// with the prolongation first on the way up, the others one each; the last down launch
+// restricts.  Their number has to be even (the depth's result ends in x), so the two pairs are
+// used only together.  (nu1 + nu2 is even, so single sweeps always end in x.)
+struct SweepPlan {
+    int ndown, nup;
+    bool down2, up2;
+};
+
+static SweepPlan sweep_plan(const DimLists& D, int d, int nu1, int nu2, bool load) {
+    SweepPlan t;
+    t.down2 = D.fz_m3[d] > 0 && nu1 >= 2 && !load;
+    t.up2 = D.fz_m3[d] > 0 && nu2 >= 2;
+    if (t.down2 != t.up2) t.down2 = t.up2 = false;
+    t.ndown = nu1 - (t.down2 ? 1 : 0);
+    t.nup = nu2 - (t.up2 ? 1 : 0);
+    return t;
+}
+
 // Fused-tile prefixes of the down / up lists (2D) and the sweep lists (3D) for the
 // plan's launch shape.
 void finish_fused(const Plan& p, DimLists& D) {
@@ -201,6 +220,15 @@ void finish_fused(const Plan& p, DimLists& D) {
     } else {
         D.levels3 = 0;
         while (D.levels3 < nd && tiles2(D.sw3[D.levels3].levels) > p.ncu) ++D.levels3;
+        // A level 0 that needs single sweeps beside or instead of the two-sweep launches (nu other
+        // than 2, or plain V-cycles from the iterate) marches only past four rounds of tiles:
+        // its single sweeps are few workgroups of many planes.  Plain V-cycles in FP64, a step of
+        // 64^3: 2.08 ms marching, 1.49 ms in tiles; of 80^3: 1.98 and 1.62 ms.  (The next level's
+        // tiles are an eighth: none of the levels marches then.)
+        if (D.levels3 > 0 && tiles2(D.sw3[0].levels) <= 4 * p.ncu) {
+            const SweepPlan t = sweep_plan(D, 0, p.opts.nu1, p.opts.nu2, !p.krylov && !p.mixed);
+            if (t.ndown + t.nup > (t.down2 ? 2 : 0)) D.levels3 = 0;
+        }
     }
     D.thr_dn.assign(D.down2.size(), kBlock);
     D.thr_up.assign(D.up2.size(), kBlock);
@@ -708,25 +736,6 @@ static void layout(Plan& p) {
         off = align_up(off + (size_t)d.n[0] * d.n[1] * d.n[2] * (p.mixed ? 4 : 8));
     }
     p.ws_bytes = off;
-}
-
-// The launches of a depth's marching sweeps: two sweeps from zero first on the way down, two
-// with the prolongation first on the way up, the others one each; the last down launch
-// restricts.  Their number has to be even (the depth's result ends in x): an odd one takes
-// the way up's pair apart.  (nu1 + nu2 is even, so single sweeps always end in x.)
-struct SweepPlan {
-    int ndown, nup;
-    bool down2, up2;
-};
-
-static SweepPlan sweep_plan(const DimLists& D, int d, int nu1, int nu2, bool load) {
-    SweepPlan t;
-    t.down2 = D.fz_m3[d] > 0 && nu1 >= 2 && !load;
-    t.up2 = D.fz_m3[d] > 0 && nu2 >= 2;
-    if (t.down2 != t.up2) t.down2 = t.up2 = false;
-    t.ndown = nu1 - (t.down2 ? 1 : 0);
-    t.nup = nu2 - (t.up2 ? 1 : 0);
-    return t;
 }
 
 // The launches of a depth's small-level passes: sweeps per launch, down then up.  A launch takes
