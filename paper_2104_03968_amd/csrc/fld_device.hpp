@@ -102,7 +102,7 @@ __host__ __device__ inline int32_t sweep3_tiles(const int32_t n[3], bool restr, 
 // its ring of kM3R LDS planes.  One position a thread, the two colour classes in wavefronts of
 // their own (m3_class threads each): 1024 threads in FP32; in FP64 the planes in flight take
 // more registers than 128, which leaves 768 threads and a smaller window.
-constexpr int kM3H = 4, kM3R = 6;
+constexpr int kM3H = 4, kM3R = 6, kM3MaxFz = 64;
 __host__ __device__ constexpr int m3_px(int word) { return 40; }
 __host__ __device__ constexpr int m3_py(int word) { return 24; }
 __host__ __device__ constexpr int m3_class(int word) { return 512; }
@@ -136,8 +136,11 @@ constexpr int kPqPY = 15;
 // row-march CG direction update (2D level 0): windows of kMarchNP - 4 interior columns
 // and kPq2Rows rows
 constexpr int kPq2Rows = 32;
-// plane depth of the level-0 3D sweep that also forms r . z
+// planes of a partial of r . z in the level-0 3D passes that form it, so that a grid's sum does not
+// depend on what else the plan holds: the depth of a single sweep's windows, and the groups within
+// the windows of a two-sweep march, whose depth (a multiple) is chosen for the whole plan
 constexpr int kRz3Fz = 32;
+constexpr int kRz3Group = 8;
 __host__ __device__ inline int32_t pq2_tiles(const int32_t n[3], int fz) {
     return ((n[0] + kMarchNP - 5) / (kMarchNP - 4)) * ((n[1] + fz - 1) / fz);
 }
@@ -388,8 +391,9 @@ void launch_sweep3(bool fp32, const LevelDesc* L, const GridState* S, JobList jl
                    int from_xs, int fz, int nblk, hipStream_t s, int rz = 0);
 // Two red-black sweeps of a 3D level per launch, as a z-march of fz (even) planes a window,
 // reading x (or xs with from_xs) and writing the other; mode 0: from zero, restricting; 1: from
-// zero; 2: from the iterate plus the prolonged coarse correction, colour 1 first, with rz as in
-// launch_sweep3.
+// zero; 2: from the iterate plus the prolonged coarse correction, colour 1 first, with rz (FP64, fz
+// a multiple of kRz3Group) one partial of b . x per columns of a window and kRz3Group planes,
+// numbered as windows of that depth.
 void launch_march3(bool fp32, const LevelDesc* L, const GridState* S, JobList jl, int mode, int from_xs, int fz,
                    hipStream_t s, int rz = 0);
 // Small-level passes: ns (1..3) red-black sweeps per launch, colour c0 first, reading x (or xs

@@ -2211,7 +2211,8 @@ k_sweep3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
 //   M3_DOWN   from zero, and the residual restricted onto the coarse level
 //   M3_ZERO   from zero
 //   M3_UP     from the iterate plus the prolonged coarse correction, colour 1 first; with
-//             rz (level 0 under FP64 CG) also one partial of b . x per window
+//             rz (level 0 under FP64 CG) also one partial of b . x per kRz3Group planes of a
+//             window: the sum's order does not depend on the depth, which is the plan's
 // Updates and residuals have the per-colour kernels' operand order, s / dg formed by div_by
 // from the reciprocal of the position's first update, so the results are bitwise theirs.
 // What bounds it: the chain of a step's four dependent updates between two barriers (the
@@ -2243,6 +2244,7 @@ template <typename T, int MODE>
 struct March3Lds {
     March3Slot<T> s[kM3R];
     T res[2][MODE == M3_DOWN ? m3_py(sizeof(T)) : 1][m3_px(sizeof(T))];        // (also what the window's edge reads past x)
+    double rz[MODE == M3_UP ? kM3MaxFz / kRz3Group : 1][2 * m3_class(sizeof(T)) / 64];   // by group of planes and wavefront
 };
 
 // A 32-bit byte offset that the compiler does not fold into a 64-bit base kept in registers.
@@ -2253,7 +2255,7 @@ __device__ __forceinline__ V load_at(gptr<T> plane, uint32_t off) {
 }
 
 template <typename T, int MODE, int CLS>
-__device__ __forceinline__ double march3_body(March3Lds<T, MODE>& t, const LevelDesc& d, const LevelDesc& cL,
+__device__ __forceinline__ void march3_body(March3Lds<T, MODE>& t, const LevelDesc& d, const LevelDesc& cL,
                                               int from_xs, int lt, int fz, int rz) {
     using V2 = T __attribute__((ext_vector_type(2)));
     using Slot = March3Slot<T>;
@@ -2392,7 +2394,15 @@ __device__ __forceinline__ double march3_body(March3Lds<T, MODE>& t, const Level
         constexpr int q4 = (q + NB - 4) % NB, q5 = (q + NB - 5) % NB, q6 = (q + NB - 6) % NB;
         if constexpr (UP && std::is_same_v<T, double>) {
             // (the position itself is final one step before its plane)
-            if (rz && inner && zt - 4 >= z0 && zt - 4 < z1) rzacc += B[q4] * X[q4];
+            const int p4 = zt - 4;
+            if (rz && p4 >= z0 && p4 < z1) {                   // uniform
+                if (inner) rzacc += B[q4] * X[q4];
+                if ((p4 - z0) % kRz3Group == kRz3Group - 1 || p4 + 1 == z1) {
+                    const double sum = wave_sum(rzacc);
+                    if ((threadIdx.x & 63) == 0) t.rz[(p4 - z0) / kRz3Group][threadIdx.x >> 6] = sum;
+                    rzacc = 0.0;
+                }
+            }
         }
         // plane zt - 5 is final
         const int p5 = zt - 5;
@@ -2456,7 +2466,6 @@ __device__ __forceinline__ double march3_body(March3Lds<T, MODE>& t, const Level
     for (; zb + NB <= ze; zb += NB) unroll<NB>([&](auto Qc) { step(Qc, zb + decltype(Qc)::value); });
     unroll_while<0, NB - 1>([&](int i) { return zb + i < ze; },
                             [&](auto Qc) { step(Qc, zb + decltype(Qc)::value); });
-    return rzacc;
 }
 
 template <typename T, int MODE>
@@ -2474,15 +2483,16 @@ k_march3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
         const LevelDesc& cL = L[d.coarse];
         const int lt = tt - job_start(jl, jb);
         // (both classes pass the same barriers: one a step)
-        double acc = cls == 0 ? march3_body<T, MODE, 0>(t, d, cL, from_xs, lt, fz, rz)
-                              : march3_body<T, MODE, 1>(t, d, cL, from_xs, lt, fz, rz);
+        if (cls == 0) march3_body<T, MODE, 0>(t, d, cL, from_xs, lt, fz, rz);
+        else march3_body<T, MODE, 1>(t, d, cL, from_xs, lt, fz, rz);
         __syncthreads();                                       // the slots are reused by the next window
         if constexpr (MODE == M3_UP && std::is_same_v<T, double>) {
-            if (rz) {
-                double unused = 0.0;
-                block_sum2<2 * CT>(acc, unused, &t.s[0].w0[0][0][0]);
-                if (threadIdx.x == 0) d.part[lt] = acc;
-                __syncthreads();
+            const int cols = march3_tiles(d.n, sizeof(T), d.n[2]), g0 = lt / cols * (fz / kRz3Group);
+            const int ng = min(fz / kRz3Group, (d.n[2] + kRz3Group - 1) / kRz3Group - g0);
+            if (rz && threadIdx.x < ng) {
+                double sum = 0.0;
+                for (int w = 0; w < 2 * CT / 64; ++w) sum += t.rz[threadIdx.x][w];
+                d.part[(g0 + threadIdx.x) * cols + lt % cols] = sum;
             }
         }
     }

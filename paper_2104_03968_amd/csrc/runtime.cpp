@@ -152,6 +152,12 @@ static SweepPlan sweep_plan(const DimLists& D, int d, int nu1, int nu2, bool loa
     return t;
 }
 
+// Whether the last level-0 up launch of a V-cycle from zero is a two-sweep march.
+static bool rz_in_pair(const Plan& p, const DimLists& D) {
+    const SweepPlan t = sweep_plan(D, 0, p.opts.nu1, p.opts.nu2, false);
+    return t.up2 && t.nup == 1;
+}
+
 // Fused-tile prefixes of the down / up lists (2D) and the sweep lists (3D) for the
 // plan's launch shape.
 void finish_fused(const Plan& p, DimLists& D) {
@@ -183,7 +189,10 @@ void finish_fused(const Plan& p, DimLists& D) {
         D.fz_m3[dpt] = 0;
         bool fits = true;
         for (int32_t li : m.levels) fits = fits && (int64_t)p.levels[li].n[0] * p.levels[li].n[1] <= (1 << 28);
-        for (int fz : {4, 8, 16, 32, 64}) {
+        // (level 0 where it also forms r . z: whole groups of its partials)
+        const bool rz = dpt == 0 && p.krylov && !p.mixed && !D.fin_fused && !D.fold;
+        for (int fz : {4, 8, 16, 32, kM3MaxFz}) {
+            if (rz && fz % kRz3Group) continue;
             int64_t tiles = 0;
             for (int32_t li : m.levels) tiles += march3_tiles(p.levels[li].n, word, fz);
             const int64_t cost = ((tiles + p.ncu - 1) / p.ncu) * (fz + 9);
@@ -208,12 +217,16 @@ void finish_fused(const Plan& p, DimLists& D) {
         for (int32_t li : levels) n += tile_tiles(p.levels[li].n, 3, 2);
         return n;
     };
-    // the last level-0 up sweep under FP64 CG also forms r . z; it marches a fixed plane
-    // depth, so a grid's partials (one per window) do not depend on the tuned one
+    // the last level-0 up launch under FP64 CG also forms r . z, so that a grid's partials do not
+    // depend on the plan: a two-sweep march per kRz3Group planes of its windows, a single sweep
+    // in windows of kRz3Fz planes
     D.rz3.levels = D.sw3.empty() ? std::vector<int32_t>{} : D.sw3[0].levels;
     D.rz3.prefix.assign(1, 0);
-    for (int32_t li : D.rz3.levels)
-        D.rz3.prefix.push_back(D.rz3.prefix.back() + sweep3_tiles(p.levels[li].n, false, kRz3Fz));
+    for (int32_t li : D.rz3.levels) {
+        const int32_t* n = p.levels[li].n;
+        D.rz3.prefix.push_back(D.rz3.prefix.back() + (rz_in_pair(p, D) ? march3_tiles(n, p.mixed ? 4 : 8, kRz3Group)
+                                                                       : sweep3_tiles(n, false, kRz3Fz)));
+    }
     const int nd = (int)D.sw3.size();
     if (p.sweep3_levels > 0) {
         D.levels3 = std::min(p.sweep3_levels, nd);
@@ -888,7 +901,7 @@ static void enqueue_mg(Plan& p, DimLists& D, hipStream_t s, bool rz0 = false) {
 }
 
 // Whether the level-0 up pass of the CG preconditioner also forms the r . z partials
-// (one per window, summed by a k_finalize over the pass's list): FP64 (b is r), reductions
+// (one per window or group of planes, summed by a k_finalize over rz_list): FP64 (b is r), reductions
 // that finish in a k_finalize launch anyway, and every grid's level 0 in the pass (a grid
 // without a coarse level has none): in 2D a row march, in 3D a fused last sweep (a plain
 // one: nu2 >= 2).
@@ -900,10 +913,8 @@ static bool rz_in_march(const Plan& p, const DimLists& D) {
     return D.fused && !D.march.empty() && D.march[0] && D.mfz[0] == kMarchFz &&
            D.mup[0].levels.size() == D.l0_cell.levels.size();
 }
-static const JobList& rz_list(const Plan& p, const DimLists& D) {
-    if (D.dim == 2) return D.mup[0].dev;
-    const SweepPlan t = sweep_plan(D, 0, p.opts.nu1, p.opts.nu2, false);
-    return t.up2 && t.nup == 1 ? D.m3[0].dev : D.rz3.dev;
+static const JobList& rz_list(const DimLists& D) {
+    return D.dim == 2 ? D.mup[0].dev : D.rz3.dev;
 }
 
 // Full-multigrid cycle on the V-cycle's level-0 arrays (Sec. 3.4 starts each solve
@@ -965,7 +976,7 @@ static void enqueue_cycle(Plan& p, hipStream_t s) {
             // next kernel's blocks (D.fold), or in a k_finalize launch
             const bool fin_launch = !ff && !D.fold;
             if (rzm) {
-                launch_finalize(p.dL, p.dS, rz_list(p, D), FIN_RZ, rt, mc, s);
+                launch_finalize(p.dL, p.dS, rz_list(D), FIN_RZ, rt, mc, s);
             } else {
                 launch_cg_rz(dim, p.mixed, p.dL, p.dS, l0, ff ? FIN_RZ : -1, rt, mc, cell_blocks(p), s);
                 if (fin_launch) launch_finalize(p.dL, p.dS, l0, FIN_RZ, rt, mc, s);

@@ -29,3 +29,16 @@ def test_same_bits_as_launches_per_colour(kw, precision):
     (a,), (sa,), _ = run_step([g], precision=precision, **kw)
     (b,), (sb,), _ = run_step([g], precision=precision, fused=0, **kw)
     assert np.array_equal(a, b) and sa["cycles"] == sb["cycles"]
+
+
+# r . z of a large grid comes from the two-sweep march, whose plane depth is the plan's: 64 beside
+# the other grid in the first and the last case, 8 in place of 32 in the second; the direction
+# pass' depth is the same alone and beside it
+@pytest.mark.parametrize("shape,other", [((160, 160, 160), (64, 64, 64)), ((136, 136, 136), (96, 96, 96)),
+                                         ((136, 136, 136), (208, 208, 208))])
+def test_sums_do_not_depend_on_the_depth_of_the_windows(shape, other):
+    a, b = W.random_grid(shape, 99600, dt=2e-3), W.random_grid(other, 99601, dt=1e-3)
+    (xa,), (sa,), _ = run_step([a])
+    xb, sb, _ = run_step([a, b])
+    assert sa["cycles"] == sb[0]["cycles"] and sa["rel_residual"] == sb[0]["rel_residual"]
+    assert np.array_equal(xa, xb[0])
