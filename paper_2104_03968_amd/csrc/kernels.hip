@@ -2806,7 +2806,6 @@ struct TailGeom {
     float rnx;           // 1 / nx
     int32_t ox, ob;      // (the first level has no b here)
     int32_t pm;          // neighbour mask (nb_mask): periodic axes, continuous faces
-    int32_t flat;        // cells of a colour counted along the whole level (nx odd), not row by row
 };
 
 
@@ -2815,11 +2814,12 @@ struct TailGeom {
 __device__ __forceinline__ int fdiv(int q, float rd) { return (int)(((float)q + 0.5f) * rd); }
 
 // Cell m among the cells of `color`: its coordinates, and whether there is one.  Rows count
-// ceil(nx / 2) cells of a colour each; `flat` levels of odd nx take every second cell of the
-// level (of a plane, where its cells are even in number), which counts no missing ones.
-template <int DIM>
+// ceil(nx / 2) cells of a colour each; with FLAT, a level of odd nx whose rows do not fit takes
+// every second cell of the level (of a plane, where its cells are even in number), which counts
+// no missing ones.
+template <int DIM, bool FLAT = false>
 __device__ __forceinline__ bool tail_cell(const TailGeom& g, int color, int m, int& i, int& j, int& k) {
-    if (g.flat) {
+    if (FLAT && tail_half(g.n) > kTailCells / 2) {
         int c = 2 * m + color;
         if (DIM == 3 && !(g.n[1] & 1)) {
             const int sz = g.n[0] * g.n[1], p = m / (sz / 2);
@@ -2854,7 +2854,7 @@ struct TailCells {
 
     // tid: this thread among the NT that share the level; spare: an element of x that no cell
     // has; with_b: the right-hand side too (else set_b later)
-    template <int NT>
+    template <int NT, bool FLAT = false>
     __device__ __forceinline__ void load(const TailGeom& g, const LevelDesc& d, bool has_a, int spare, int tid,
                                          bool with_b) {
         const gptr<T> w0 = as_global(Arr<T>::w(d, 0)), w1 = as_global(Arr<T>::w(d, 1));
@@ -2867,7 +2867,7 @@ struct TailCells {
 #pragma unroll
             for (int u = 0; u < CPC; ++u) {
                 int i, j, k;
-                const bool ok = tail_cell<DIM>(g, q, tid + u * NT, i, j, k);
+                const bool ok = tail_cell<DIM, FLAT>(g, q, tid + u * NT, i, j, k);
                 const int c = ok ? i + j * sy + k * sz : 0;
                 at[q][u] = ok ? c : spare;
                 const int ijk[3] = {i, j, k}, st[3] = {1, sy, sz};
@@ -3099,8 +3099,8 @@ __device__ __forceinline__ void tail_cg(const TailCells<DIM, T, BC, CPC>& c, con
 }
 
 // The coarsest level's solve by the whole workgroup, from x.  op: its operator where it does not
-// split (faces, then the Dirichlet couplings).
-template <int DIM, typename T, bool BC>
+// split (faces, then the Dirichlet couplings).  FLAT: of a single level.
+template <int DIM, typename T, bool BC, bool FLAT = false>
 __device__ __forceinline__ void tail_coarsest(const TailGeom& g, const LevelDesc& d, const T* bs, const T* op, bool has_a,
                                               bool split, T* x, T* y, int spare, double* sh) {
     constexpr int NT = kTailThreads, CPC = kTailMaxCoarsest / 2 / NT;
@@ -3118,7 +3118,7 @@ __device__ __forceinline__ void tail_coarsest(const TailGeom& g, const LevelDesc
         }
     }
     TailCells<DIM, T, BC, CPC> c;
-    c.template load<NT>(g, d, has_a, spare, threadIdx.x, false);
+    c.template load<NT, FLAT>(g, d, has_a, spare, threadIdx.x, false);
     c.set_b(g, bs);
     tail_cg<DIM, T, BC, NT, CPC>(c, g, has_a, x, y, sh);
 }
@@ -3154,7 +3154,6 @@ struct TailLead {
         g.rnx = 1.0f / (float)d.n[0];
         g.rny = 1.0f / (float)d.n[1];
         g.pm = BC ? nb_mask(d) : 0;
-        g.flat = 0;
         x = o;
         b = o + g.ncell;
         for (int q = 0; q < 3; ++q) w[q] = o + (2 + q) * g.ncell;   // (unused past DIM)
@@ -3284,7 +3283,6 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
         t.rnx = 1.0f / (float)nown[0];
         t.rny = 1.0f / (float)nown[1];
         t.pm = pm_own;
-        t.flat = tail_half(t.n) > kTailCells / 2;
         t.ox = pad;
         t.ob = total + cells[0] + pad;
         for (int j = 0; j < mo; ++j) {
@@ -3313,7 +3311,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
     // else its operator past every level's b: each iteration on all cells reads it (from global
     // memory, a step of 100 x 180 cells with periodic x and a 25 x 45 coarsest level took 925 us
     // in place of 853, one of 45 x 45 with continuous faces 660 in place of 328)
-    const int oop = gl.ob + gl.ncell;
+    const int oop = BC ? 2 * total - pad + cells[0] : 0;
     if (BC && !split) {
         const LevelDesc& d = L[first + nl - 1];
         const int na = DIM + (has_a ? 1 : 0);
@@ -3322,7 +3320,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
             for (int c = threadIdx.x; c < gl.ncell; c += NT) base[oop + a * gl.ncell + c] = src[c];
         }
     }
-    T* const lead_at = base + oop + (split ? 0 : (DIM + (has_a ? 1 : 0)) * gl.ncell);
+    T* const lead_at = base + 2 * total - pad + cells[0] + (split ? 0 : (DIM + (has_a ? 1 : 0)) * gl.ncell);
     auto lead_up = [&] {
         // (its arrays are still in LDS: the struct alone is formed again)
         __syncthreads();
@@ -3341,7 +3339,7 @@ k_tail(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList
             if (warm) x0[c] = gx[c];
         }
         __syncthreads();
-        tail_coarsest<DIM, T, BC>(g0, d0, base + g0.ob, base + oop, has_a, split, x0, y, spare - g0.ox, sh);
+        tail_coarsest<DIM, T, BC, true>(g0, d0, base + g0.ob, base + oop, has_a, split, x0, y, spare - g0.ox, sh);
         if (lead) return lead_up();
         __syncthreads();
         for (int c = threadIdx.x; c < g0.ncell; c += NT) gx[c] = x0[c];
