@@ -98,19 +98,15 @@ __host__ __device__ inline int32_t sweep3_tiles(const int32_t n[3], bool restr, 
     return ((n[0] + fx - 1) / fx) * ((n[1] + fy - 1) / fy) * ((n[2] + fz - 1) / fz);
 }
 
-// Two-sweep z-march (k_march3): a window of m3_px x m3_py positions, with a halo of four, and
+// Two-sweep z-march (k_march3): a window of kM3PX x kM3PY positions, with a halo of four, and
 // its ring of kM3R LDS planes.  One position a thread, the two colour classes in wavefronts of
-// their own (m3_class threads each): 1024 threads in FP32; in FP64 the planes in flight take
-// more registers than 128, which leaves 768 threads and a smaller window.
+// their own (kM3Class threads each).
 constexpr int kM3H = 4, kM3R = 6, kM3MaxFz = 64;
-__host__ __device__ constexpr int m3_px(int word) { return 40; }
-__host__ __device__ constexpr int m3_py(int word) { return 24; }
-__host__ __device__ constexpr int m3_class(int word) { return 512; }
-static_assert(m3_px(4) / 2 * (m3_py(4) + 1) <= m3_class(4) && (m3_px(4) / 2 + 1) * m3_py(4) <= m3_class(4) &&
-                  m3_px(8) / 2 * (m3_py(8) + 1) <= m3_class(8) && (m3_px(8) / 2 + 1) * m3_py(8) <= m3_class(8),
+constexpr int kM3PX = 40, kM3PY = 24, kM3Class = 512;
+static_assert(kM3PX / 2 * (kM3PY + 1) <= kM3Class && (kM3PX / 2 + 1) * kM3PY <= kM3Class,
               "a class' positions, and a row or a pair of columns of faces more");
-__host__ __device__ inline int32_t march3_tiles(const int32_t n[3], int word, int fz) {
-    const int fx = m3_px(word) - 2 * kM3H, fy = m3_py(word) - 2 * kM3H;
+__host__ __device__ inline int32_t march3_tiles(const int32_t n[3], int fz) {
+    const int fx = kM3PX - 2 * kM3H, fy = kM3PY - 2 * kM3H;
     return ((n[0] + fx - 1) / fx) * ((n[1] + fy - 1) / fy) * ((n[2] + fz - 1) / fz);
 }
 

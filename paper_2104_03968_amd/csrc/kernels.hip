@@ -2192,7 +2192,7 @@ k_sweep3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
 // Two red-black sweeps per launch of a large 3D level: the z-march of k_sweep3 with four
 // half sweeps in flight, so that a level's iterate, right-hand side and faces are read
 // once per two sweeps (a V(2,2) cycle's level pass moves 11 words a cell instead of 23, and
-// memory bandwidth bounds the single sweeps).  A workgroup owns a window of m3_px x m3_py
+// memory bandwidth bounds the single sweeps).  A workgroup owns a window of kM3PX x kM3PY
 // positions (32 x 16 interior columns and a halo of four), one position a thread, and
 // marches through fz planes; at step zt half sweep k updates plane zt - k.  The positions
 // of one colour class, (x + y) even or odd, belong to the first eight wavefronts, the
@@ -2234,7 +2234,7 @@ __device__ __forceinline__ T div_by(T s, T d, T r) {
 
 template <typename T>
 struct March3Slot {                                          // one plane of the ring, by class
-    static constexpr int PY = m3_py(sizeof(T)), KW = m3_px(sizeof(T)) / 2;
+    static constexpr int PY = kM3PY, KW = kM3PX / 2;
     T w0[2][PY][KW];
     T w1[2][PY + 1][KW];
     T x[2][PY][KW];
@@ -2243,8 +2243,8 @@ struct March3Slot {                                          // one plane of the
 template <typename T, int MODE>
 struct March3Lds {
     March3Slot<T> s[kM3R];
-    T res[2][MODE == M3_DOWN ? m3_py(sizeof(T)) : 1][m3_px(sizeof(T))];        // (also what the window's edge reads past x)
-    double rz[MODE == M3_UP ? kM3MaxFz / kRz3Group : 1][2 * m3_class(sizeof(T)) / 64];   // by group of planes and wavefront
+    T res[2][MODE == M3_DOWN ? kM3PY : 1][kM3PX];        // (also what the window's edge reads past x)
+    double rz[MODE == M3_UP ? kM3MaxFz / kRz3Group : 1][2 * kM3Class / 64];   // by group of planes and wavefront
 };
 
 // A 32-bit byte offset that the compiler does not fold into a 64-bit base kept in registers.
@@ -2259,7 +2259,7 @@ __device__ __forceinline__ void march3_body(March3Lds<T, MODE>& t, const LevelDe
                                               int from_xs, int lt, int fz, int rz) {
     using V2 = T __attribute__((ext_vector_type(2)));
     using Slot = March3Slot<T>;
-    constexpr int PX = m3_px(sizeof(T)), PY = m3_py(sizeof(T)), CT = m3_class(sizeof(T));
+    constexpr int PX = kM3PX, PY = kM3PY, CT = kM3Class;
     constexpr int KX = PX / 2, KW = Slot::KW, H = kM3H, R = kM3R, FX = PX - 2 * H, FY = PY - 2 * H;
     constexpr int C0 = MODE == M3_UP ? 1 : 0;
     constexpr bool UP = MODE == M3_UP, DOWN = MODE == M3_DOWN;
@@ -2469,10 +2469,10 @@ __device__ __forceinline__ void march3_body(March3Lds<T, MODE>& t, const LevelDe
 }
 
 template <typename T, int MODE>
-__global__ void __launch_bounds__(2 * m3_class(sizeof(T)))
+__global__ void __launch_bounds__(2 * kM3Class)
 k_march3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int from_xs, int fz, int rz) {
     __shared__ March3Lds<T, MODE> t;
-    constexpr int CT = m3_class(sizeof(T));
+    constexpr int CT = kM3Class;
     const int cls = __builtin_amdgcn_readfirstlane(threadIdx.x >= CT);
     const XcdOrder order(jl.total);
     for (int k = order.first(); order.more(k); k += order.per) {
@@ -2487,7 +2487,7 @@ k_march3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
         else march3_body<T, MODE, 1>(t, d, cL, from_xs, lt, fz, rz);
         __syncthreads();                                       // the slots are reused by the next window
         if constexpr (MODE == M3_UP && std::is_same_v<T, double>) {
-            const int cols = march3_tiles(d.n, sizeof(T), d.n[2]), g0 = lt / cols * (fz / kRz3Group);
+            const int cols = march3_tiles(d.n, d.n[2]), g0 = lt / cols * (fz / kRz3Group);
             const int ng = min(fz / kRz3Group, (d.n[2] + kRz3Group - 1) / kRz3Group - g0);
             if (rz && threadIdx.x < ng) {
                 double sum = 0.0;
@@ -4672,8 +4672,8 @@ void launch_march3(bool fp32, const LevelDesc* L, const GridState* S, JobList jl
     const int g = blocks_for_xcd(jl.total, jl.total);          // one window a workgroup
 #define FLD_MARCH3(M_)                                                                                              \
     do {                                                                                                           \
-        if (fp32) hipLaunchKernelGGL((k_march3<float, M_>), dim3(g), dim3(2 * m3_class(4)), 0, s, L, S, jl, from_xs, fz, rz);   \
-        else hipLaunchKernelGGL((k_march3<double, M_>), dim3(g), dim3(2 * m3_class(8)), 0, s, L, S, jl, from_xs, fz, rz);       \
+        if (fp32) hipLaunchKernelGGL((k_march3<float, M_>), dim3(g), dim3(2 * kM3Class), 0, s, L, S, jl, from_xs, fz, rz);   \
+        else hipLaunchKernelGGL((k_march3<double, M_>), dim3(g), dim3(2 * kM3Class), 0, s, L, S, jl, from_xs, fz, rz);       \
     } while (0)
     if (mode == M3_DOWN) FLD_MARCH3(M3_DOWN);
     else if (mode == M3_ZERO) FLD_MARCH3(M3_ZERO);

@@ -184,7 +184,6 @@ void finish_fused(const Plan& p, DimLists& D) {
         // two-sweep windows: the plane depth of fewest block steps (fz and nine more); a plane
         // has to stay below 4 GB (32-bit offsets)
         HostList& m = D.m3[dpt];
-        const int word = p.mixed ? 4 : 8;
         int64_t best = -1;
         D.fz_m3[dpt] = 0;
         bool fits = true;
@@ -194,13 +193,13 @@ void finish_fused(const Plan& p, DimLists& D) {
         for (int fz : {4, 8, 16, 32, kM3MaxFz}) {
             if (rz && fz % kRz3Group) continue;
             int64_t tiles = 0;
-            for (int32_t li : m.levels) tiles += march3_tiles(p.levels[li].n, word, fz);
+            for (int32_t li : m.levels) tiles += march3_tiles(p.levels[li].n, fz);
             const int64_t cost = ((tiles + p.ncu - 1) / p.ncu) * (fz + 9);
             if (fits && (best < 0 || cost < best)) { best = cost; D.fz_m3[dpt] = fz; }
         }
         m.prefix.assign(1, 0);
         for (int32_t li : m.levels)
-            m.prefix.push_back(m.prefix.back() + march3_tiles(p.levels[li].n, word, D.fz_m3[dpt] ? D.fz_m3[dpt] : 64));
+            m.prefix.push_back(m.prefix.back() + march3_tiles(p.levels[li].n, D.fz_m3[dpt] ? D.fz_m3[dpt] : kM3MaxFz));
         a.prefix.assign(1, 0);
         r.prefix.assign(1, 0);
         for (int32_t li : a.levels)
@@ -224,7 +223,7 @@ void finish_fused(const Plan& p, DimLists& D) {
     D.rz3.prefix.assign(1, 0);
     for (int32_t li : D.rz3.levels) {
         const int32_t* n = p.levels[li].n;
-        D.rz3.prefix.push_back(D.rz3.prefix.back() + (rz_in_pair(p, D) ? march3_tiles(n, p.mixed ? 4 : 8, kRz3Group)
+        D.rz3.prefix.push_back(D.rz3.prefix.back() + (rz_in_pair(p, D) ? march3_tiles(n, kRz3Group)
                                                                        : sweep3_tiles(n, false, kRz3Fz)));
     }
     const int nd = (int)D.sw3.size();
