@@ -81,12 +81,14 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-def dominant_kernel(fld, ndim: int, word: int, fused: bool, fused3: bool, march: bool = False):
+def dominant_kernel(fld, ndim: int, word: int, fused: bool, fused3: bool, march: bool = False, pairs: bool = False):
     """The kernel that dominates a step and its algorithmic bytes per cell of level 0.
 
     2D (fused level kernels, LDS tiles or row-marching windows): the level-0 up pass
     reads the down pass's iterate, b, both face arrays and a quarter-size coarse
-    correction, and writes x: (5 + 1/4) words.  3D fused sweeps: one whole red-black sweep reads x, b and
+    correction, and writes x: (5 + 1/4) words.  3D two-sweep marches (pairs): the level-0
+    up launch reads x, b, the three face arrays and an eighth-size coarse correction once and
+    writes x: (6 + 1/8) words.  3D fused single sweeps: one whole red-black sweep reads x, b and
     the three face arrays once and writes x: 6 words.  3D per-colour kernels:
     one half sweep reads x of every cell, b of the updated half, every face
     weight (each face touches one cell of each colour) and writes x of the
@@ -94,6 +96,8 @@ def dominant_kernel(fld, ndim: int, word: int, fused: bool, fused3: bool, march:
     """
     if ndim == 2 and fused:
         return fld.FLD_KERNEL_UP, "k_march2" if march else "k_up2", word * 5 + word / 4
+    if ndim == 3 and fused3 and pairs:
+        return fld.FLD_KERNEL_MARCH3, "k_march3", word * 6 + word / 8
     if ndim == 3 and fused3:
         return fld.FLD_KERNEL_SWEEP3, "k_sweep3", word * 6
     return fld.FLD_KERNEL_SMOOTH, "k_smooth", word * (2 + ndim)
@@ -176,6 +180,7 @@ def measured_traffic(cfg: str, kname: str, ctype: str, launch: dict):
     sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
     # the launch parameters the dominant kernel's own dispatch depends on
     keys = {"k_sweep3": ("tile_depth", "max_blocks"),
+            "k_march3": (),
             "k_up2": ("tile_rows_up", "tile_wide", "max_blocks"),
             "k_march2": ("max_blocks",),
             "k_smooth": ("max_blocks",)}.get(kname, ("tile_rows", "tile_wide", "max_blocks", "tile_depth",
@@ -434,8 +439,10 @@ def run_timed(fld, torch, args, cfg, grids, has_gas, precision, dev, steps, warm
         nuc = o.nu_coarse or 0
         # the fused 2D level kernels take 1 to 3 sweeps; other counts run per colour
         fused2 = bool(o.fused) and all(1 <= v <= 3 for v in (o.nu1, o.nu2, nuc or o.nu1, nuc or o.nu2))
+        # level 0 of a 3D plan marches two sweeps a launch from zero and from a corrected iterate
+        pairs = tuning["fused3_levels"] > 0 and min(o.nu1, o.nu2) >= 2 and (bool(o.krylov) or word == 4)
         kid, kname, bpc = dominant_kernel(fld, ndim, word, fused2, bool(tuning["fused3"]),
-                                          tuning.get("march_levels", 0) > 0)
+                                          tuning.get("march_levels", 0) > 0, pairs)
         ms, cells = plan.profile(kid, 0, args.profile_reps, stream)
         achieved = bpc * cells / (ms * 1e-3) / 1e9
         log(f"bench {cfg}: level-0 {kname} {ms * 1e3:.2f} us for {cells} cells ({bpc} B/cell) -> {achieved:.0f} GB/s")

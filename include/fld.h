@@ -413,6 +413,8 @@ int32_t fld_imex_step(fld_plan_t plan, double* const* E, double* const* eps,
 #define FLD_KERNEL_TAIL      9   /* the LDS tail of every grid                             */
 #define FLD_KERNEL_SWEEP3   10   /* fused 3D: one red-black sweep from the stored iterate at `level` */
 #define FLD_KERNEL_MG       11   /* the multigrid part of one V-cycle (every level, no CG update) */
+#define FLD_KERNEL_MARCH3   12   /* fused 3D: prolongation + two sweeps in one march at `level`, where
+                                    the V-cycles run it (else INVALID_ARG)                         */
 
 /* Launch shape of a bound plan, and where it came from. */
 typedef struct fld_tuning {

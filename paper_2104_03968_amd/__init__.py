@@ -73,6 +73,7 @@ FLD_KERNEL_UP = 8
 FLD_KERNEL_TAIL = 9
 FLD_KERNEL_SWEEP3 = 10
 FLD_KERNEL_MG = 11
+FLD_KERNEL_MARCH3 = 12
 FLD_CYCLE_ITERATION = 0
 FLD_CYCLE_MG = 1
 FLD_CYCLE_FMG = 2

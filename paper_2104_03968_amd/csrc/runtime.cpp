@@ -1602,6 +1602,12 @@ static int profile_kernel(Plan& p, int kernel, int level, int reps, hipStream_t 
                           int64_t* cells) {
     const int G = p.ngrids();
     int64_t nc = 0;
+    // the marching sweeps of a level's V-cycles (none: no up2)
+    auto marches = [&](const DimLists& D) {
+        if (!(level >= 0 && level < D.maxdepth && D.fused3 && p.sweep3 && level < D.levels3)) return SweepPlan{};
+        return sweep_plan(D, level, level == 0 ? p.opts.nu1 : p.nuc1, level == 0 ? p.opts.nu2 : p.nuc2,
+                          level == 0 && !p.krylov && !p.mixed);
+    };
     // collect the lists the kernel runs over (2D and 3D grids launch separately)
     for (auto& D : p.dl) {
         if (D.l0_cell.empty()) continue;
@@ -1615,6 +1621,7 @@ static int profile_kernel(Plan& p, int kernel, int level, int reps, hipStream_t 
             case FLD_KERNEL_UP: if (has_level && D.fused) l = &D.up2[level]; break;
             case FLD_KERNEL_TAIL: l = D.tail.empty() ? nullptr : &D.tail; break;
             case FLD_KERNEL_SWEEP3: if (has_level && D.fused3) l = &D.sw3[level]; break;
+            case FLD_KERNEL_MARCH3: if (marches(D).up2) l = &D.m3[level]; break;
             default: l = &D.l0_cell; break;
         }
         if (!l) continue;
@@ -1674,8 +1681,14 @@ static int profile_kernel(Plan& p, int kernel, int level, int reps, hipStream_t 
                     if (has_level && D.fused3)
                         launch_sweep3(p.mixed, p.dL, p.dS, D.sw3[level].dev, 0, 0, 0, D.fz_s[level], p.nblk, s);
                     break;
+                case FLD_KERNEL_MARCH3:
+                    if (const SweepPlan t = marches(D); t.up2)
+                        launch_march3(p.mixed, p.dL, p.dS, D.m3[level].dev, 2, t.ndown % 2, D.fz_m3[level], s,
+                                      level == 0 && t.nup == 1 && rz_in_march(p, D));
+                    break;
                 case FLD_KERNEL_TAIL:
-                    launch_tail(D.dim, p.mixed, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, D.tail_lead, p.nuc1, p.nuc2, 0, s);
+                    launch_tail(D.dim, p.mixed, p.nb_bc(), p.dL, p.dS, D.tail.dev, D.tail_smem, D.tail_cpc, D.tail_lead,
+                                p.nuc1, p.nuc2, 0, s);
                     break;
                 default: break;
             }
@@ -2069,7 +2082,7 @@ int32_t fld_plan_cycle_bytes(fld_plan_t plan, int32_t what, double* bytes, int64
 
 int32_t fld_profile_kernel(fld_plan_t plan, int32_t kernel, int32_t level, int32_t reps, void* stream,
                            double* avg_ms, int64_t* cells) {
-    if (!plan || !avg_ms || !cells || reps < 1 || kernel < 0 || kernel > FLD_KERNEL_MG)
+    if (!plan || !avg_ms || !cells || reps < 1 || kernel < 0 || kernel > FLD_KERNEL_MARCH3)
         return FLD_ERR_INVALID_ARG;
     Plan& p = plan->p;
     if (!p.ws) return FLD_ERR_NO_WORKSPACE;

@@ -42,3 +42,16 @@ def test_sums_do_not_depend_on_the_depth_of_the_windows(shape, other):
     xb, sb, _ = run_step([a, b])
     assert sa["cycles"] == sb[0]["cycles"] and sa["rel_residual"] == sb[0]["rel_residual"]
     assert np.array_equal(xa, xb[0])
+
+
+def test_profile_of_the_march():
+    plan = fld.Plan([(64, 64, 64)])
+    ms, cells = plan.profile(fld.FLD_KERNEL_MARCH3, 0, 5)
+    assert ms > 0 and cells == 64 ** 3
+    with pytest.raises(fld.FLDError):
+        plan.profile(fld.FLD_KERNEL_MARCH3, 1, 5)              # a level of tiles
+    plan.close()
+    plan = fld.Plan([(64, 64, 64)], krylov=0)
+    with pytest.raises(fld.FLDError):
+        plan.profile(fld.FLD_KERNEL_MARCH3, 0, 5)
+    plan.close()
