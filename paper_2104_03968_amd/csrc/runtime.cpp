@@ -388,11 +388,10 @@ static size_t lead_bytes(const Plan& p, int g, int t) {
 //  * where the levels above the tail can only sweep per colour, so that the lead level's launches
 //    cost more than its sweeps on one compute unit (64^2 in FP32 with continuous faces: 669 us
 //    without it, 536 us with; 128 such grids: 1406 and 807 us);
-//  * whole 3D grids (14^3 in FP64: 232 and 172 us; 128 of them: 1046 and 730 us);
-//  * whole 2D grids of up to 2 kTailCells cells in FP32 with zero-flux faces (64^2: 337 and 325 us;
-//    512 of them: 3099 and 2744 us; but 72^2: 293 and 351 us).
-// Not others: 60^2 in FP64 274 and 328 us, 32^3 in FP32 361 and 411 us.  fld_opts.fused has no say:
-// its choices give the same bits, and a tail sweeps level 0 as often as the coarse levels.
+//  * whole 3D grids (14^3 in FP64: 232 and 172 us; 128 of them: 1046 and 730 us).
+// Not others: 60^2 in FP64 274 and 328 us, 32^3 in FP32 361 and 411 us; 29 FP32 grids of 64^2 to
+// 512^2 wait for the lead levels of the few smallest (1476 and 1597 us).  fld_opts.fused has no
+// say: its choices give the same bits, and a tail sweeps level 0 as often as the coarse levels.
 static void choose_tails(Plan& p) {
     p.tail_lev.assign(p.ngrids(), -1);
     for (int g = 0; g < p.ngrids(); ++g) {
@@ -401,11 +400,9 @@ static void choose_tails(Plan& p) {
             if (tail_fits(p, g, l)) t = l;
         if (t < 1 || tail_bytes(p, g, t) + lead_bytes(p, g, t) > kTailLdsBudget) continue;
         const LevelDesc& f = p.levels[p.level0[g] + t - 1];
-        const int64_t n = (int64_t)f.n[0] * f.n[1] * f.n[2];
-        if (n <= kTailCells) continue;                         // (the tail knows a lead level by its size)
+        if ((int64_t)f.n[0] * f.n[1] * f.n[2] <= kTailCells) continue;   // (the tail knows a lead level by its size)
         const bool per_colour = !(f.ndim == 2 ? fuses2(p) : fuses3(p)) && !tiles_bc(p);
-        const bool whole = t == 1 && (f.ndim == 3 || (p.mixed && !p.nb_bc() && n <= 2 * kTailCells));
-        if (per_colour || whole) --t;
+        if (per_colour || (t == 1 && f.ndim == 3)) --t;
     }
 }
 

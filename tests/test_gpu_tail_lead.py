@@ -57,11 +57,11 @@ def test_whole_3d_grids(shape, precision, bc, fmg):
     assert step_and_launches(shape, bc, precision=precision, fmg=fmg) == launches
 
 
+# whole 2D grids with fused passes have no lead level
 @pytest.mark.parametrize("shape", [(46, 46), (64, 64), (4, 1024), (1024, 4), (8, 512), (52, 78)])
-def test_whole_2d_grids_in_fp32(shape):
-    assert step_and_launches(shape, "zero_flux", precision=1) == 1
-    if min(shape) > 4:                                         # (plain V-cycles stall on 4 x 1024 with any kernels)
-        assert step_and_launches(shape, "zero_flux", precision=1, krylov=0) == 1
+@pytest.mark.parametrize("precision", [0, 1])
+def test_whole_2d_grids(shape, precision):
+    assert step_and_launches(shape, "zero_flux", precision=precision) == 3
 
 
 @pytest.mark.parametrize("precision", [0, 1])
