@@ -2210,9 +2210,10 @@ k_sweep3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
 // between are zero.  Modes:
 //   M3_DOWN   from zero, and the residual restricted onto the coarse level
 //   M3_ZERO   from zero
-//   M3_UP     from the iterate plus the prolonged coarse correction, colour 1 first; with
-//             rz (level 0 under FP64 CG) also one partial of b . x per kRz3Group planes of a
-//             window: the sum's order does not depend on the depth, which is the plan's
+//   M3_UP     from the iterate plus the prolonged coarse correction, colour 1 first
+//   M3_UP_RZ  (level 0 under FP64 CG) also one partial of b . x per kRz3Group planes of a
+//             window: the sum's order does not depend on the depth, which is the plan's (a mode
+//             of its own: behind a flag it cost the other up marches 8 % at 64^3)
 // Updates and residuals have the per-colour kernels' operand order, s / dg formed by div_by
 // from the reciprocal of the position's first update, so the results are bitwise theirs.
 // What bounds it: the chain of a step's four dependent updates between two barriers (the
@@ -2221,7 +2222,7 @@ k_sweep3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
 // down 240 / 167 us where two single sweeps took 385 / 234 us, up 281 / 190 us against
 // 392 / 220 us.
 // ---------------------------------------------------------------------------
-enum March3Mode : int { M3_DOWN = 0, M3_ZERO = 1, M3_UP = 2 };
+enum March3Mode : int { M3_DOWN = 0, M3_ZERO = 1, M3_UP = 2, M3_UP_RZ = 3 };
 
 // s / d from r = 1 / d (correctly rounded): one correction step of the quotient, exact in
 // the normal range.
@@ -2244,7 +2245,7 @@ template <typename T, int MODE>
 struct March3Lds {
     March3Slot<T> s[kM3R];
     T res[2][MODE == M3_DOWN ? kM3PY : 1][kM3PX];        // (also what the window's edge reads past x)
-    double rz[MODE == M3_UP ? kM3MaxFz / kRz3Group : 1][2 * kM3Class / 64];   // by group of planes and wavefront
+    double rz[MODE == M3_UP_RZ ? kM3MaxFz / kRz3Group : 1][2 * kM3Class / 64];   // by group of planes and wavefront
 };
 
 // A 32-bit byte offset that the compiler does not fold into a 64-bit base kept in registers.
@@ -2256,13 +2257,13 @@ __device__ __forceinline__ V load_at(gptr<T> plane, uint32_t off) {
 
 template <typename T, int MODE, int CLS>
 __device__ __forceinline__ void march3_body(March3Lds<T, MODE>& t, const LevelDesc& d, const LevelDesc& cL,
-                                              int from_xs, int lt, int fz, int rz) {
+                                              int from_xs, int lt, int fz) {
     using V2 = T __attribute__((ext_vector_type(2)));
     using Slot = March3Slot<T>;
     constexpr int PX = kM3PX, PY = kM3PY, CT = kM3Class;
     constexpr int KX = PX / 2, KW = Slot::KW, H = kM3H, R = kM3R, FX = PX - 2 * H, FY = PY - 2 * H;
-    constexpr int C0 = MODE == M3_UP ? 1 : 0;
-    constexpr bool UP = MODE == M3_UP, DOWN = MODE == M3_DOWN;
+    constexpr bool RZ = MODE == M3_UP_RZ, UP = MODE == M3_UP || RZ, DOWN = MODE == M3_DOWN;
+    constexpr int C0 = UP ? 1 : 0;
     // planes are loaded PF steps ahead (FP64 up: two would spill)
     constexpr int PF = UP && sizeof(T) == 8 ? 1 : 2, NB = 10;
     constexpr bool KEEP = !(UP && sizeof(T) == 8);             // reciprocals kept (else they spill)
@@ -2335,7 +2336,7 @@ __device__ __forceinline__ void march3_body(March3Lds<T, MODE>& t, const LevelDe
         B[q] = load_at<T>(bg + min(max(min(gk, z1 + H), 0), n2 - 1) * sz, c);
     };
     T racc = T(0);
-    double rzacc = 0.0;
+    [[maybe_unused]] double rzacc = 0.0;
     const int rci = m % (FX / 2), rcj = m / (FX / 2);    // coarse cell of the restriction's owners
     const int CI = (gx0 + H) / 2 + rci, CJ = (gy0 + H) / 2 + rcj;
     const bool rown = DOWN && CLS == 0 && m < (FX / 2) * (FY / 2) && CI < (n0 >> 1) && CJ < (n1 >> 1);
@@ -2392,10 +2393,10 @@ __device__ __forceinline__ void march3_body(March3Lds<T, MODE>& t, const LevelDe
             });
         }
         constexpr int q4 = (q + NB - 4) % NB, q5 = (q + NB - 5) % NB, q6 = (q + NB - 6) % NB;
-        if constexpr (UP && std::is_same_v<T, double>) {
+        if constexpr (RZ) {
             // (the position itself is final one step before its plane)
             const int p4 = zt - 4;
-            if (rz && p4 >= z0 && p4 < z1) {                   // uniform
+            if (p4 >= z0 && p4 < z1) {                         // uniform
                 if (inner) rzacc += B[q4] * X[q4];
                 if ((p4 - z0) % kRz3Group == kRz3Group - 1 || p4 + 1 == z1) {
                     const double sum = wave_sum(rzacc);
@@ -2470,7 +2471,7 @@ __device__ __forceinline__ void march3_body(March3Lds<T, MODE>& t, const LevelDe
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(2 * kM3Class)
-k_march3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int from_xs, int fz, int rz) {
+k_march3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobList jl, int from_xs, int fz) {
     __shared__ March3Lds<T, MODE> t;
     constexpr int CT = kM3Class;
     const int cls = __builtin_amdgcn_readfirstlane(threadIdx.x >= CT);
@@ -2483,13 +2484,13 @@ k_march3(const LevelDesc* __restrict__ L, const GridState* __restrict__ S, JobLi
         const LevelDesc& cL = L[d.coarse];
         const int lt = tt - job_start(jl, jb);
         // (both classes pass the same barriers: one a step)
-        if (cls == 0) march3_body<T, MODE, 0>(t, d, cL, from_xs, lt, fz, rz);
-        else march3_body<T, MODE, 1>(t, d, cL, from_xs, lt, fz, rz);
+        if (cls == 0) march3_body<T, MODE, 0>(t, d, cL, from_xs, lt, fz);
+        else march3_body<T, MODE, 1>(t, d, cL, from_xs, lt, fz);
         __syncthreads();                                       // the slots are reused by the next window
-        if constexpr (MODE == M3_UP && std::is_same_v<T, double>) {
+        if constexpr (MODE == M3_UP_RZ) {
             const int cols = march3_tiles(d.n, d.n[2]), g0 = lt / cols * (fz / kRz3Group);
             const int ng = min(fz / kRz3Group, (d.n[2] + kRz3Group - 1) / kRz3Group - g0);
-            if (rz && threadIdx.x < ng) {
+            if (threadIdx.x < ng) {
                 double sum = 0.0;
                 for (int w = 0; w < 2 * CT / 64; ++w) sum += t.rz[threadIdx.x][w];
                 d.part[(g0 + threadIdx.x) * cols + lt % cols] = sum;
@@ -4670,14 +4671,13 @@ void launch_march3(bool fp32, const LevelDesc* L, const GridState* S, JobList jl
     const double words = mode == M3_DOWN ? 5.0 + 2.0 / 8.0 : (mode == M3_ZERO ? 5.0 : 6.0 + 1.0 / 8.0);
     if (acct_add(jl.cells * (fp32 ? 4.0 : 8.0) * words)) return;
     const int g = blocks_for_xcd(jl.total, jl.total);          // one window a workgroup
-#define FLD_MARCH3(M_)                                                                                              \
-    do {                                                                                                           \
-        if (fp32) hipLaunchKernelGGL((k_march3<float, M_>), dim3(g), dim3(2 * kM3Class), 0, s, L, S, jl, from_xs, fz, rz);   \
-        else hipLaunchKernelGGL((k_march3<double, M_>), dim3(g), dim3(2 * kM3Class), 0, s, L, S, jl, from_xs, fz, rz);       \
-    } while (0)
+#define FLD_MARCH3_T(T_, M_) hipLaunchKernelGGL((k_march3<T_, M_>), dim3(g), dim3(2 * kM3Class), 0, s, L, S, jl, from_xs, fz)
+#define FLD_MARCH3(M_) do { if (fp32) FLD_MARCH3_T(float, M_); else FLD_MARCH3_T(double, M_); } while (0)
     if (mode == M3_DOWN) FLD_MARCH3(M3_DOWN);
     else if (mode == M3_ZERO) FLD_MARCH3(M3_ZERO);
+    else if (rz && !fp32) FLD_MARCH3_T(double, M3_UP_RZ);
     else FLD_MARCH3(M3_UP);
+#undef FLD_MARCH3_T
 #undef FLD_MARCH3
 }
 
