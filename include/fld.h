@@ -493,9 +493,12 @@ int32_t fld_profile_kernel(fld_plan_t plan, int32_t kernel, int32_t level, int32
  * its inputs and its result; until then they wait (no request is refused for a
  * full arena unless it could never fit).  Admitted requests iterate together:
  * every multigrid phase is one launch over all resident requests, and requests
- * join and leave at iteration boundaries.  A request's result is the same
- * whether it runs alone or among others (same kernels, tiles and reduction
- * orders per grid).  All server calls are thread-safe. */
+ * join and leave at iteration boundaries.  A request runs the same kernels and
+ * tiles alone and among others, and its result is the same bit for bit while
+ * the resident requests have at most 8192 level-0 tiles (1024 cells each) and
+ * none more than 2048; beyond that the sums of the CG scalars may be taken in
+ * another order and the result agrees to rounding.  All server calls are
+ * thread-safe. */
 typedef struct fld_server_s* fld_server_t;
 
 typedef struct fld_server_opts {
