@@ -86,3 +86,16 @@ def test_same_bits_without_fused_passes(shape, precision):
         (a,), (sa,), _ = run_step([g], precision=precision, krylov=krylov)
         (b,), (sb,), _ = run_step([g], precision=precision, krylov=krylov, fused=0)
         assert np.array_equal(a, b) and sa["cycles"] == sb["cycles"]
+
+
+# a lead level beside them sends every grid's tail to another instantiation of the kernel
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("kind", ["zero_flux", "periodic"])
+def test_grids_beside_a_lead_level_keep_their_bits(kind, precision):
+    shapes = [(8, 8, 8), (12, 12, 12), (24, 24, 24), (11, 11, 11), (40, 24, 32), (13, 12, 13), (3, 5, 7)]
+    kw = dict(precision=precision, bc=[CODE[kind]] * 6)
+    gs = [W.random_grid(s, 99100 + i, dt=2e-3) for i, s in enumerate(shapes)]
+    xb, sb, _ = run_step(gs + [W.random_grid((14, 14, 14), 99190, dt=2e-3)], **kw)
+    for i, g in enumerate(gs):
+        (xa,), (sa,), _ = run_step([g], **kw)
+        assert np.array_equal(xa, xb[i]) and sa["cycles"] == sb[i]["cycles"], shapes[i]
