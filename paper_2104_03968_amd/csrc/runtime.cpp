@@ -233,14 +233,15 @@ void finish_fused(const Plan& p, DimLists& D) {
         D.levels3 = 0;
         while (D.levels3 < nd && tiles2(D.sw3[D.levels3].levels) > p.ncu) ++D.levels3;
         // A level 0 that needs single sweeps beside or instead of the two-sweep launches (nu other
-        // than 2, or plain V-cycles from the iterate) marches only past four rounds of tiles:
-        // its single sweeps are few workgroups of many planes.  Plain V-cycles in FP64, a step of
-        // 64^3: 2.08 ms marching, 1.49 ms in tiles; of 80^3: 1.98 and 1.62 ms.  (The next level's
-        // tiles are an eighth: none of the levels marches then.)
-        if (D.levels3 > 0 && tiles2(D.sw3[0].levels) <= 4 * p.ncu) {
-            const SweepPlan t = sweep_plan(D, 0, p.opts.nu1, p.opts.nu2, !p.krylov && !p.mixed);
-            if (t.ndown + t.nup > (t.down2 ? 2 : 0)) D.levels3 = 0;
-        }
+        // than 2, or plain V-cycles from the iterate) marches only past four rounds of tiles, and
+        // with more single-sweep windows of its many planes than a third of the compute units.
+        // Plain V-cycles in FP64, a step of 64^3: 1.88 ms marching, 1.34 ms in tiles; of 80^3: 1.98
+        // and 1.62 ms; of 104^3 (80 windows): 2.87 ms marching, 2.34 ms per colour; of 120^3 (88)
+        // with three sweeps each way: 2.27 and 2.52 ms.  (None of the levels marches then.)
+        const SweepPlan t = D.levels3 > 0 ? sweep_plan(D, 0, p.opts.nu1, p.opts.nu2, !p.krylov && !p.mixed) : SweepPlan{};
+        if (t.ndown + t.nup > (t.down2 ? 2 : 0) &&
+            (tiles2(D.sw3[0].levels) <= 4 * p.ncu || 3 * D.sw3[0].prefix.back() <= p.ncu))
+            D.levels3 = 0;
     }
     D.thr_dn.assign(D.down2.size(), kBlock);
     D.thr_up.assign(D.up2.size(), kBlock);

@@ -1,6 +1,6 @@
 """Which 3D plans march on level 0: with two sweeps each way from zero (conjugate gradients) those of
 more tiles than compute units; where single sweeps are needed (plain V-cycles from the iterate, other
-sweep counts) those of more than four rounds of tiles.  The steps agree with the launches per colour
+sweep counts) those of more than four rounds of tiles and of windows enough.  The steps agree with the launches per colour
 on every bit either way."""
 import numpy as np
 import pytest
@@ -14,11 +14,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("shape,kw,levels", [((64, 64, 64), {}, 1), ((64, 64, 64), dict(krylov=0), 0),
                                              ((64, 64, 64), dict(nu1=4, nu2=4), 0), ((80, 72, 80), dict(krylov=0), 0),
-                                             ((64, 64, 64), dict(nu1=1, nu2=1), 0), ((96, 96, 96), dict(krylov=0), 1),
+                                             ((64, 64, 64), dict(nu1=1, nu2=1), 0), ((100, 100, 100), dict(krylov=0), 0),
+                                             ((128, 128, 128), dict(krylov=0), 1), ((100, 100, 100), {}, 1),
                                              ((64, 64, 64), dict(krylov=0, fused3_levels=1), 1)])
 def test_level_0_marches_where_its_launches_fill_the_card(shape, kw, levels):
     plan = fld.Plan([shape], **kw)
-    assert plan.tuning()["fused3_levels"] == levels
+    assert min(1, plan.tuning()["fused3_levels"]) == levels
     plan.close()
 
 
