@@ -1,4 +1,4 @@
-"""Grids of a single level too large for the LDS tail: under conjugate gradients every outer
+"""Grids of a single level, too large for the LDS tail or just in it: under conjugate gradients every outer
 iteration solves them directly, from zero, to a 1e-6 residual.
 
 The mixed-precision plan makes the same solve in FP32 arrays, so FP64 takes no more outer
@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 # up to and past the 4096 cells whose vectors sit in LDS; beside a grid with fused passes
 CASES = [[(47, 47)], [(1025, 3)], [(3, 1025)], [(67, 67)], [(13, 13, 13)], [(257, 3, 3)], [(17, 17, 17)],
-         [(1025, 3), (128, 96)], [(257, 3, 3), (72, 64, 64)]]
+         [(1025, 3), (128, 96)], [(257, 3, 3), (72, 64, 64)],
+         [(45, 45)], [(13, 12, 13), (72, 64, 64)]]             # single levels at the tail's limit
 
 
 @pytest.mark.parametrize("shapes", CASES)
