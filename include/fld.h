@@ -161,7 +161,9 @@ typedef struct fld_opts {
                              through the planes, the coarser ones several sweeps of a
                              small tile per launch (per-colour kernels where that takes
                              many tiles); 0 = the levels with more such tiles than compute
-                             units [0].  3D grids use both when fused is not 0, nu1, nu2
+                             units, and none where level 0 also needs single sweeps (nu1
+                             or nu2 other than 2, plain FP64 V-cycles) and has few windows
+                             for them [0].  3D grids use both when fused is not 0, nu1, nu2
                              >= 1 and nu1 + nu2 is even.  tile_rows, tile_wide, max_blocks, tile_depth and
                              fused3_levels must be 0 with autotune                  */
     double  bc_grad[6];   /* per face: the prescribed gradient of FLD_BC_FIXED_GRADIENT
