@@ -150,9 +150,10 @@ typedef struct fld_opts {
                              along the rows on depths with at least four windows per
                              compute unit; 2 = tiles only; 3 = march wherever fused;
                              0: one kernel per colour sweep and per transfer.  Every
-                             choice gives the same results bit for bit, but in plans of
-                             more than 8192 level-0 tiles under FP64 conjugate gradients:
-                             the marching up pass forms r . z there too, in another order [1] */
+                             choice gives the same results bit for bit, but in FP64 plans
+                             of more than 8192 level-0 tiles (of 1024 cells), or with a grid
+                             of more than 2048, under conjugate gradients: the marching up
+                             pass forms r . z there too, in another order [1]      */
     int32_t tile_rows;    /* fused 2D tile rows: 4, 8, 16 or 32; 0 = 8 [0]          */
     int32_t tile_wide;    /* fused 2D tile width: 0 = 64 cells, 1 = 128 cells less
                              the halo (a colour cell per lane of a 64-lane wave) [0].
